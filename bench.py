@@ -64,7 +64,8 @@ def algorithmic_cost(widths, steps, include_output=False):
         by["next"] += E0 * (8.0 + 2 * 8.0 * nw + 2.0)
         for j, st in enumerate(steps[s0:s0 + N]):
             V, E, S, Kv = (float(v) for v in st)
-            by["select"] += 2.0 * E + 4.0 * S
+            # the splitting edges of a layer's later neurons are listed by the pairing's launches
+            by["pair" if j else "select"] += 2.0 * E + 4.0 * S
             # split: read SPL id, edge, the two endpoint values at neuron j, two rows (coords, carried
             # pre-activations, signs), write one row, two edges, two next-crossings, and 2-face keys
             # (32-bit key per slot, hash + entry per key). Carried columns: all N of the layer (the next
@@ -803,8 +804,8 @@ def main():
             fam_roof[f]["mfma_frac"] = flops / s_ / 1e12 / FP64_PEAK_TFLOPS
         if f == "pair":
             fam_roof[f]["note"] = ("12 B per key slot and 25 B per pair (edge, next crossing, one sign word of each "
-                                   "new vertex); two launches per neuron of a few microseconds each, so latency, "
-                                   "not bytes, bounds it")
+                                   "new vertex), and the next neuron's compaction (2 B per edge, 4 B per splitting "
+                                   "edge), which shares the pairing's one or two launches per neuron")
     sub_ms = sum(med_ms[f] for f in ("next", "select", "split", "sort", "pair"))
     subdivision = {"bytes": b8_total, "ms": sub_ms, "GB_per_s": b8_total / (sub_ms / 1e3) / 1e9,
                    "hbm_frac": b8_total / (sub_ms / 1e3) / 1e9 / HBM_PEAK_GBS,

@@ -186,11 +186,13 @@ int pcx_complex_device(const pcx_complex *cx, void **coords, void **signs, void 
  * few microseconds of stream time. */
 #define PCX_K_GEMM 0     /* per-layer pre-activation evaluation (step 1) */
 #define PCX_K_NEXT 1     /* per-layer first-crossing scan of every edge (steps 2-3) */
-#define PCX_K_SELECT 2   /* per-step splitting-edge compaction (step 3) */
+#define PCX_K_SELECT 2   /* splitting-edge compaction (step 3) on its own: a layer's first neuron, redone steps,
+                            and every step with PCX_PAIR_SORT (else part of PCX_K_PAIR) */
 #define PCX_K_SPLIT 3    /* per-step interpolation, split, 2-face keys (steps 4-5) */
 #define PCX_K_SORT 4     /* per-step radix sort of 2-face keys (step 5, PCX_PAIR_SORT) */
 #define PCX_K_PAIR 5     /* per-step pairing into intersecting edges (step 5; with PCX_PAIR_HASH the
-                            table inserts run inside PCX_K_SPLIT) */
+                            table inserts run inside PCX_K_SPLIT, and the pairing's launches also list
+                            the next neuron's splitting edges) */
 #define PCX_K_COUNT 6
 #define PCX_K_ALL ((1 << PCX_K_COUNT) - 1)
 int pcx_complex_kernel_time(const pcx_complex *cx, int32_t family, double *ms, int64_t *launches);

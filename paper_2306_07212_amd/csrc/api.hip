@@ -577,8 +577,9 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
         if ((rc = x.arena.alloc(&p, Wd * sizeof(uint64_t)))) return rc;
         x.b.VALID = (const uint64_t *)p;
         HIPCHK(hipMemcpyAsync(p, valid.data(), Wd * sizeof(uint64_t), hipMemcpyHostToDevice, st));
-        if ((rc = x.arena.alloc(&p, (size_t)kNextBlocks * sizeof(int)))) return rc;
+        if ((rc = x.arena.alloc(&p, (size_t)kSelWords * sizeof(int)))) return rc;
         x.b.SELCNT = (int *)p;
+        x.b.SELTAB = (int2 *)(x.b.SELCNT + kNextBlocks);
     }
     double *dbox = nullptr;
     if (box) {
@@ -673,7 +674,8 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
     if ((rc = x.ensure_step((size_t)Shint, (size_t)Shint * x.P))) return rc;
     x.tables_reset = false;  // new tables are zero, and so are the counters
     int64_t V = (int64_t)V0, E = (int64_t)E0;
-    int64_t Sgrid = 64;  // split count the split launch is shaped for (any count is covered)
+    int64_t Sgrid = 64;  // split count the step's launches are shaped for (any count is covered)
+    int64_t Sseen = 0;   //   from the layer's largest so far, once the host has seen it
     int64_t Eseen = 0;   // latest edge count the host has seen (a lower bound: shapes the compaction)
     int64_t prevE = -1, prevS = 0;  // sort pairing: the host's own step log
     bool pairs_logged = false;      //   the previous step's pair count was taken at a layer start
@@ -724,6 +726,7 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
         g.hkeep = hbits < 64 ? (1ull << hbits) - 1ull : ~0ull;
         g.fbits = fbits;
         g.verify = o.verify_pairs ? 1 : 0;
+        g.next = x.pair_mode == PAIR_HASH && j + 1 < g.Nl ? j + 1 : -1;
         g.Vcap = (int)std::min<size_t>(x.Vcap, INT32_MAX);
         g.Ecap = (int)std::min<size_t>(x.Ecap, INT32_MAX);
         g.Kcap = (int)std::min<size_t>(x.Kcap, INT32_MAX);
@@ -767,8 +770,7 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
         if (nslots > (int64_t)x.Kcap) return fail(PCX_ERR_DEVICE, "internal error: key slots beyond the storage");
         if ((r = x.put_ctr(CTR_PFLAGS, 0)) || (r = x.put_ctr(CTR_PFAIL, 0x7fffffff))) return r;
         if ((r = x.ensure_exact((size_t)nslots))) return r;
-        const int grid = full_grids ? kSelBlocks : pair_grid(nslots);
-        launch_exact_pair(x.b, g, (int)nslots, grid, st);
+        launch_exact_pair(x.b, g, (int)nslots, full_grids, st);
         HIPCHK(hipGetLastError());
         if ((r = x.drain())) return r;
         if (x.hctr[CTR_FLAGS] || x.hctr[CTR_PFLAGS])
@@ -784,9 +786,11 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
     };
 
     int l = 0, j = 0;
+    int nlist = 0;  // chunks of the next step's split list that the last pairing wrote (0: none to be used)
     bool started = false;
     while (true) {
         if (!started) {
+            nlist = 0;
             // layer start (or the end): every enqueued step is done
             if ((rc = x.drain())) return rc;
             int f;
@@ -816,7 +820,9 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
             Eseen = 0;
             // launch shape from the previous step's count until this layer's own largest is known
             const int64_t Slast = step0[l] > 0 ? x.hctr[CTR_S] : 0;
-            Sgrid = Slast + Slast / 4 + 64;
+            // (and, as early steps grow fast, the largest step that the network is known or predicted to have)
+            Sgrid = std::max<int64_t>(Slast + Slast / 4, (int64_t)Sinit) + 64;
+            Sseen = 0;
             if (lagged && (rc = x.put_ctr(CTR_SMAX, 0))) return rc;
             if (!lagged && step0[l] > 0) {
                 // before pruning can change the edge count
@@ -884,7 +890,10 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
                     HIPCHK(hipEventSynchronize(x.evsnap[other]));
                     const int *c = x.hsnap[other];
                     x.snap_at[other] = -1;
-                    Sgrid = std::max<int64_t>(Sgrid, c[CTR_SMAX] + c[CTR_SMAX] / 4 + 64);
+                    if (c[CTR_SMAX] > 0) {  // (steps of this layer done by then)
+                        Sseen = std::max<int64_t>(Sseen, c[CTR_SMAX] + c[CTR_SMAX] / 4 + 64);
+                        Sgrid = Sseen;
+                    }
                     Eseen = std::max<int64_t>({Eseen, c[CTR_E], c[CTR_E + 1]});
                     if (c[CTR_FLAGS] || c[CTR_PFLAGS]) {
                         // stop running ahead: exact counts, then redo, resume or report
@@ -896,6 +905,7 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
                             if (fresh || f < step0[l] || f > s)
                                 return fail(PCX_ERR_DEVICE, "internal error: bad failing step");
                             j = f - step0[l];
+                            nlist = 0;  // a redone step lists its edges again
                             continue;
                         }
                     }
@@ -911,12 +921,17 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
             if ((rc = x.mark(PCX_K_NEXT, false))) return rc;
             if ((rc = x.mark(PCX_K_SELECT, true))) return rc;
             launch_gather(x.b, (int)E, par, s, st);
-        } else {
+            if ((rc = x.mark(PCX_K_SELECT, false))) return rc;
+            nlist = 1;
+        } else if (nlist == 0) {
+            // (sort pairing, and hash steps redone: the pairing before them listed nothing)
             if ((rc = x.mark(PCX_K_SELECT, true))) return rc;
             launch_select(x.b, (uint16_t)j, par, s,
                           full_grids ? kSelBlocks : select_grid(lagged ? std::max(Eseen, E) : E), st);
+            if ((rc = x.mark(PCX_K_SELECT, false))) return rc;
+            nlist = 1;
         }
-        if ((rc = x.mark(PCX_K_SELECT, false))) return rc;
+        g.nlist = nlist;
         HIPCHK(hipGetLastError());
         int64_t S = 0;
         if (!lagged) {
@@ -928,6 +943,7 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
                 // the previous step's pairing was redone: this step's compaction again
                 if (fresh || f < step0[l] || f > s) return fail(PCX_ERR_DEVICE, "internal error: bad failing step");
                 j = f - step0[l];
+                nlist = 0;
                 continue;
             }
             S = x.hctr[CTR_S];
@@ -943,15 +959,16 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
             if ((rc = grow_for(V, E, S, 1, (size_t)S))) return rc;
             blocks = split_blocks(full_grids ? INT32_MAX : (int)S, N);
             g = geom(l, j);  // capacities may have grown
+            g.nlist = nlist;
         }
-        const int pgrid = full_grids ? kSelBlocks : pair_grid(lagged ? Sgrid * x.P : S * x.P);
+        nlist = 0;
         hipEvent_t es, ee;
         if ((rc = x.launch_events(PCX_K_SPLIT, es, ee))) return rc;
         launch_split(x.b, g, blocks, st, es, ee);
         HIPCHK(hipGetLastError());
         if (lagged) {
             if ((rc = x.mark(PCX_K_PAIR, true))) return rc;
-            launch_hash_pair(x.b, g, pgrid, st);
+            nlist = launch_hash_pair(x.b, g, Sgrid * x.P, std::max(Eseen, E), full_grids, st);
             if ((rc = x.mark(PCX_K_PAIR, false))) return rc;
             HIPCHK(hipGetLastError());
         } else if (S * x.P > 0) {

@@ -217,12 +217,13 @@ __device__ __forceinline__ bool slot_owner(const Bufs &b, const StepGeom &g, int
 // agree on every entry before the current neuron; check_hash: also compare the
 // stored 64-bit hashes (the hash table already matched them exactly). preA:
 // words wn .. wn+3 of sa's row, when the caller has loaded them already.
-__device__ __forceinline__ void emit_pair(const Bufs &b, const StepGeom &g, int V0, int nslots, int sa, int sb,
+// Returns the edge's first crossing in the layer (kNoCol: none).
+__device__ __forceinline__ int emit_pair(const Bufs &b, const StepGeom &g, int V0, int nslots, int sa, int sb,
                                           size_t out, bool check_hash = true, bool check_rows = true,
                                           const uint64_t *preA = nullptr) {
     if ((unsigned)sa >= (unsigned)nslots || (unsigned)sb >= (unsigned)nslots) {
         raise_flag(b.CTR, FLAG_BOUNDS);
-        return;
+        return kNoCol;
     }
     const int xa = V0 + sa / g.P, xb = V0 + sb / g.P;
     const uint64_t *Ra = b.SG + (size_t)xa * g.Wd, *Rb = b.SG + (size_t)xb * g.Wd;
@@ -261,6 +262,7 @@ __device__ __forceinline__ void emit_pair(const Bufs &b, const StepGeom &g, int 
         b.NX8[out] = col == kNoCol ? 0 : (uint8_t)col;  // col > j >= 0
     else
         b.NXT[out] = col == kNoCol ? kNone : (uint16_t)col;
+    return col;
 }
 
 // One tile of kGemmRows vertex rows x all N <= 256 outputs (see k_gemm). The

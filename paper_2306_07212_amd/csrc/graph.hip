@@ -102,7 +102,7 @@ int build(const pcx_mlp *mlp, const GraphLog &lg, GraphEntry &ge, hipStream_t cs
     size_t Tcap = 256;
     while (Tcap < 2 * Kcap) Tcap <<= 1;
     const uint64_t bytes = Vcap * 8ull * (D + Wd + ZS + 8) + Ecap * (8ull + 1 + 4 + 16) + Kcap * 12ull +
-                           Tcap * 16ull + (uint64_t)n_steps * sizeof(StepRec) + kNextBlocks * 4ull;
+                           Tcap * 16ull + (uint64_t)n_steps * sizeof(StepRec) + kSelWords * 4ull;
     if (bytes > kGraphMaxBytes) return fail(PCX_ERR_CAPACITY, "graph storage above its cap");
     if (g_graph_bytes.fetch_add(bytes) + bytes > kGraphBudget) {
         g_graph_bytes -= bytes;
@@ -128,7 +128,8 @@ int build(const pcx_mlp *mlp, const GraphLog &lg, GraphEntry &ge, hipStream_t cs
     b.PART = (uint64_t *)take(Kcap * 8);
     unsigned long long *HT[2] = {(unsigned long long *)take(Tcap * 8), (unsigned long long *)take(Tcap * 8)};
     b.CTR = (int *)take(CTR_COUNT * 4);
-    b.SELCNT = (int *)take(kNextBlocks * 4);
+    b.SELCNT = (int *)take(kSelWords * 4);
+    b.SELTAB = (int2 *)(b.SELCNT + kNextBlocks);
     b.REC = (StepRec *)take((size_t)n_steps * sizeof(StepRec));
     uint64_t *valid = (uint64_t *)take(Wd * 8);
     double *dbox = (double *)take(2 * D * 8);
@@ -165,6 +166,7 @@ int build(const pcx_mlp *mlp, const GraphLog &lg, GraphEntry &ge, hipStream_t cs
         const int Vl = (int)sl[0], El = (int)sl[1];
         if (l == 0) launch_gemm(b, ZS, b.X, D, 0, Vl, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], cs);
         else launch_gemm(b, ZS, b.Z, ZS, 1, Vl, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], cs);
+        int nlist = 1;
         for (int j = 0; j < N; ++j) {
             const int s = step0[l] + j, par = s & 1;
             const int64_t *st4 = &lg.steps[(size_t)s * 4];
@@ -191,14 +193,14 @@ int build(const pcx_mlp *mlp, const GraphLog &lg, GraphEntry &ge, hipStream_t cs
             g.Vcap = (int)Vcap;
             g.Ecap = (int)Ecap;
             g.Kcap = (int)Kcap;
+            g.next = j + 1 < N ? j + 1 : -1;
+            g.nlist = nlist;
             if (j == 0) {
                 launch_next_all(b, Vl, Wd, lw[l], lw[l + 1], El, par, s, cs);
                 launch_gather(b, El, par, s, cs);
-            } else {
-                launch_select(b, (uint16_t)j, par, s, select_grid(st4[1]), cs);
             }
             launch_split(b, g, split_blocks((int)st4[2], N), cs);
-            launch_hash_pair(b, g, pair_grid(st4[2] * P), cs);
+            nlist = launch_hash_pair(b, g, st4[2] * P, st4[1] + st4[2], false, cs);
         }
     }
     const hipError_t le = hipGetLastError();

@@ -12,7 +12,9 @@ constexpr int kSelTile = kThreads * kSelItems;
 constexpr int kScanItems = 32;           // one-byte first crossings per thread in the per-step compaction
 constexpr int kScanTile = kThreads * kScanItems;
 constexpr int kSelBlocks = 1024;         // largest grid of the per-step compaction and hash pairing
-constexpr int kNextBlocks = 8192;        // most chunks of the layer-start scan (its compaction included)
+constexpr int kNextBlocks = 4096;        // most chunks of the layer-start scan (its compaction included)
+constexpr int kListMax = 2048;           // most chunks of a split list (the scan's and the emission's)
+constexpr int kSelWords = kNextBlocks + 2 * kListMax;  // ints of SELCNT, SELTAB behind it
 constexpr int kSortItems = 8;            // keys per thread in a radix-sort tile
 constexpr int kSortTile = kThreads * kSortItems;
 constexpr int kSortBins = 256;           // 8-bit digits
@@ -100,6 +102,8 @@ struct StepGeom {
     int fbits;       // bits of the exact pass's sort key kept (64; fewer only to test its grouping)
     int verify;      // 1: also compare the two perturbed sign rows of every hash-table pair word by word
     int sbits;       // slot field width of this step's table words (slot_bits of its key slots)
+    int nlist;       // chunks of this step's split list in SELTAB (1: one gathered list)
+    int next;        // the neuron whose splitting edges the pairing also lists: j + 1, or -1 (none, or the layer's end)
 };
 
 // Log of one neuron step, written by its last kernel: counts at its start, its
@@ -117,15 +121,16 @@ struct Bufs {
     uint8_t *NX8;     // [Ecap] the same on the per-step path: 1..255, 0 = none (the layer's first
                       // neuron is never looked up: its splitting edges come from the layer-start scan)
     int *SPL;         // [Scap] split list (batched kernel)
-    int4 *SPLE;       // [Scap] split list: (edge, its two endpoints, 0)
-    int *SPLX;        // [Ecap] per-chunk match lists of the compaction (chunk c at its own edge range)
+    int4 *SPLE;       // [Scap] split list: (edge, its two endpoints, 0), each chunk of SELTAB at its own place
+    int *SPLX;        // [Ecap] per-chunk match lists of the two-pass compaction (chunk c at its own edge range)
     uint32_t *K32a, *K32b, *VALa, *VALb;  // [Kcap] radix-sort ping-pong
     uint64_t *FULL;   // [Kcap] full 64-bit 2-face hash by slot (sort pairing)
     uint32_t *PINFO;  // [Kcap] perturbed entry of the slot: word << 8 | bit << 1 | minus; kNoInfo if unused
     uint64_t *PART;   // [Kcap] partner record of each key slot (hash pairing and the exact pass)
     uint64_t *K64a, *K64b;  // [Kcap] exact pass: 64-bit sort keys (ping-pong; VALa / VALb carry the slots)
     uint32_t *HIST;   // [256 * tiles]
-    int *SELCNT;      // [kNextBlocks] per-chunk match counts of the compaction (also the pairing passes)
+    int *SELCNT;      // [kNextBlocks] per-chunk match counts of the two-pass compaction (also the pairing passes)
+    int2 *SELTAB;     // [kListMax] chunks of the current split list: (first entry in SPLE, entries), in edge order
     int *CTR;         // [CTR_COUNT]
     const uint64_t *VALID;  // [Wd] 01-pattern at every valid entry
     int2 *PQ;         // [Vcap] (V+, V-) parents of each new vertex, when the tape is recorded (else null)
@@ -146,12 +151,10 @@ void launch_gemm(const Bufs &b, int ZS, const double *in, int in_stride, int rel
 void launch_next_all(const Bufs &b, int V, int Wd, int lw0, int lw1, int E, int par, int step, hipStream_t st);
 // the compaction's second pass alone, after launch_next_all over the same E edges
 void launch_gather(const Bufs &b, int E, int par, int step, hipStream_t st);
-// splitting edges of neuron `target` from the CTR_E[par] edges: SPL, CTR_S
+// splitting edges of neuron `target` from the CTR_E[par] edges, as one list (SPLE, SELTAB[0], CTR_S)
 void launch_select(const Bufs &b, uint16_t target, int par, int step, int grid, hipStream_t st);
-// grids (<= kSelBlocks) of the per-step compaction and hash pairing for an
-// expected edge count / key-slot count: small steps take fewer workgroups
+// grid (<= kSelBlocks) of the compaction for an expected edge count: small steps take fewer workgroups
 int select_grid(int64_t edges);
-int pair_grid(int64_t slots);
 // V0, E0 and S come from the device counters of step g.step; `blocks` only
 // shapes the launch (the kernel strides over any S). The split also writes the
 // next step's vertex count.
@@ -173,17 +176,19 @@ void launch_sort64(const Bufs &b, int n, hipStream_t st, const uint64_t **keys, 
 // sort pairing (host-known counts): edges from E1 on, the edge count after the step into CTR_E[par ^ 1]
 void launch_pair(const Bufs &b, const StepGeom &g, int V0, int E1, int nslots, const uint32_t *keys,
                  const uint32_t *vals, hipStream_t st);
-// hash pairing (the split recorded the pairs): a check and count pass over the
-// key slots, then the ordered emit, all counts from the device; the emit also
-// clears the previous step's table (g.HTo), writes the next step's edge count
-// and the step's log entry
-void launch_hash_pair(const Bufs &b, const StepGeom &g, int grid, hipStream_t st);
+// hash pairing (the split recorded the pairs) and the next neuron's split list
+// (g.next >= 0), all counts from the device; it also clears the previous
+// step's table (g.HTo) and writes the next step's edge count and the step's
+// log entry. `slots` and `edges` only shape the launches (any counts are
+// covered; full: the largest grids). Returns the chunks of the next step's
+// list (its g.nlist).
+int launch_hash_pair(const Bufs &b, const StepGeom &g, int64_t slots, int64_t edges, bool full, hipStream_t st);
 // the exact pass of one step's pairing (after a pairing failure): every valid
 // key slot's 2-face sign-vector is rebuilt from its new vertex's row, sorted by
 // a 64-bit hash, and grouped by exact comparison of the rows; the pairs are
 // recorded as the table path records them and emitted by launch_hash_pair
-// with the same grid. It needs K64a/K64b, VALa/VALb and HIST for nslots keys.
-void launch_exact_pair(const Bufs &b, const StepGeom &g, int nslots, int grid, hipStream_t st);
+// (which lists nothing: g.next is ignored). It needs K64a/K64b, VALa/VALb and HIST for nslots keys.
+void launch_exact_pair(const Bufs &b, StepGeom g, int nslots, bool full, hipStream_t st);
 // fill n 64-bit words with v (a kernel, so that no memset node enters a captured graph)
 void launch_fill64(uint64_t *p, size_t n, uint64_t v, hipStream_t st);
 // the device counters at the start of an extraction from V0 vertices and E0 edges

@@ -401,7 +401,11 @@ __global__ __launch_bounds__(kThreads) void k_sel_gather(Bufs b, int par, int st
         int x = 0;
         for (int w = 0; w < kThreads / 64; ++w) x += s_w[w];
         s_base = x;
-        if (blockIdx.x == gridDim.x - 1) b.CTR[CTR_S] = x + b.SELCNT[blockIdx.x];
+        if (blockIdx.x == gridDim.x - 1) {
+            const int S = x + b.SELCNT[blockIdx.x];
+            b.CTR[CTR_S] = S;
+            b.SELTAB[0] = make_int2(0, S);
+        }
     }
     __syncthreads();
     // each entry carries its edge's endpoints, so the split starts from them
@@ -415,9 +419,8 @@ __global__ __launch_bounds__(kThreads) void k_sel_gather(Bufs b, int par, int st
     }
 }
 
-static int clamp_grid(int64_t g) { return (int)std::min<int64_t>(kSelBlocks, std::max<int64_t>(32, g)); }
-int select_grid(int64_t edges) { return clamp_grid((edges + 2047) / 2048); }
-int pair_grid(int64_t slots) { return clamp_grid((slots + 255) / 256); }
+static int clamp_grid(int64_t g, int lo) { return (int)std::min<int64_t>(kSelBlocks, std::max<int64_t>(lo, g)); }
+int select_grid(int64_t edges) { return clamp_grid((edges + 2047) / 2048, 32); }
 
 // both kernels chunk the edges by the grid they are launched with: the same one
 void launch_select(const Bufs &b, uint16_t target, int par, int step, int grid, hipStream_t st) {
@@ -536,10 +539,70 @@ __device__ __forceinline__ uint32_t table_size(int n) {
     return t;
 }
 
+// The chunks of the step's split list (SELTAB) scanned by the whole workgroup:
+// s_pre[c] = splits before chunk c, s_off[c] = its first entry less that.
+// Returns the step's split count. One gathered list (n == 1) takes no scan.
+__device__ __forceinline__ int list_scan(const Bufs &b, int n, int *s_pre, int *s_off, int *s_w) {
+    if (n == 1) return b.SELTAB[0].y;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    constexpr int kPer = kListMax / kThreads;
+    const int per = (n + kThreads - 1) / kThreads;
+    int2 e[kPer];
+    int mine = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int c = t * per + i;
+        e[i] = i < per && c < n ? b.SELTAB[c] : make_int2(0, 0);
+        mine += e[i].y;
+    }
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) s_w[wave] = incl;
+    __syncthreads();
+    int run = incl - mine, total = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) {
+        const int x = s_w[w];
+        if (w < wave) run += x;
+        total += x;
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int c = t * per + i;
+        if (i < per && c < n) {
+            s_pre[c] = run;
+            s_off[c] = e[i].x - run;
+            run += e[i].y;
+        }
+    }
+    __syncthreads();
+    return total;
+}
+
+// place of split s in SPLE: in the last chunk that starts at or before it
+// (`head` splits in the first one, which starts at entry 0)
+__device__ __forceinline__ int list_entry(int s, int n, int head, const int *s_pre, const int *s_off) {
+    if (s < head) return s;
+    int lo = 1, hi = n;  // s_pre[lo] <= s, and s_pre[hi] > s or hi == n
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (s_pre[mid] <= s) lo = mid;
+        else hi = mid;
+    }
+    return s + s_off[lo];
+}
+
 template <int G, int NC>
 __global__ __launch_bounds__(kThreads, 5) void k_split(Bufs b, StepGeom g) {
+    __shared__ int s_pre[kListMax], s_off[kListMax], s_w[kThreads / 64];
     if (step_blocked(b.CTR, g.step)) return;
-    const int V0 = b.CTR[CTR_V + g.par], E0 = b.CTR[CTR_E + g.par], S = b.CTR[CTR_S];
+    const int V0 = b.CTR[CTR_V + g.par], E0 = b.CTR[CTR_E + g.par];
+    const int head = b.SELTAB[0].y, S = list_scan(b, g.nlist, s_pre, s_off, s_w);
+    if (blockIdx.x == 0 && threadIdx.x == 0) b.CTR[CTR_S] = S;
     // every later kernel of the step writes within these bounds
     if ((int64_t)V0 + S > g.Vcap || (int64_t)E0 + (int64_t)S * g.D > g.Ecap || (int64_t)S * g.P > g.Kcap) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -565,7 +628,7 @@ __global__ __launch_bounds__(kThreads, 5) void k_split(Bufs b, StepGeom g) {
     const int grp = threadIdx.x / G;
     const int half = (threadIdx.x & 63) / G;
     for (int s = blockIdx.x * groups + grp; s < S; s += gridDim.x * groups) {
-        const int4 q = b.SPLE[s];
+        const int4 q = b.SPLE[list_entry(s, g.nlist, head, s_pre, s_off)];
         const int2 ab = make_int2(q.y, q.z);
         if (!split_entry_ok(b, q.x, E0) || !split_edge_ok(ab, V0)) {
             if (lane == 0) raise_flag(b.CTR, FLAG_BOUNDS);
@@ -865,59 +928,177 @@ void launch_pair(const Bufs &b, const StepGeom &g, int V0, int E1, int nslots, c
     hipLaunchKernelGGL(k_pair, dim3(grid), dim3(kThreads), 0, st, b, g, V0, E1, nslots, keys, vals);
 }
 
-// ---------------------------------- step 5c with the hash table
+// ---------------------------------- step 5c with the hash table, and the
+// next step's splitting edges
 //
 // The split recorded every pair as it found it (the second arrival at a
-// 2-face). Two passes over the key slots emit the pairs in the order of their
-// owner slots (the smaller slot of a pair): the first counts the owners of each
-// workgroup's chunk of slots from the slots' own records; the second adds the
-// counts of the chunks before its own, ranks the owners inside the chunk by
-// wave ballots, and checks every slot: a fresh record must be mutual, and a
-// valid slot must have one (a failure sends the step to the exact pass). The
-// edge list is therefore the same on every run and whatever the launch shapes.
-__device__ __forceinline__ void pair_chunk(int n, int &c0, int &c1) {
-    const int per = ((n + (int)gridDim.x - 1) / (int)gridDim.x + kPairItems - 1) / kPairItems * kPairItems;
-    c0 = min(n, (int)blockIdx.x * per);
+// 2-face). The emission appends the pairs' edges in the order of their owner
+// slots (the smaller slot of a pair): each workgroup takes a chunk of the
+// slots, ranks the owners inside it by wave ballots, and checks every slot: a
+// fresh record must be mutual, and a valid slot must have one (a failure sends
+// the step to the exact pass). The edge list is therefore the same on every run
+// and whatever the launch shapes. The owners before a chunk are counted either
+// by the workgroup itself, from the records of all slots before its own (small
+// steps: one launch does it all), or by a first pass over the slots.
+//
+// The same launches list the edges that the next neuron of the layer splits, so
+// that a step is two launches (three when large) and not five: the scan's
+// workgroups take the edges that were there before the pairing (every next
+// crossing is final once the split is done), the emission's those that they
+// append. Each chunk's matches go, with their endpoints, to the chunk's own
+// range of SPLE, and (first entry, count) to SELTAB; the split finds its
+// entries by a scan of that table. In large steps the scan's matches (nearly
+// all of the list) are moved to their final places beside the emission, as one
+// first chunk, so that the split looks up only the few appended edges (the
+// 768-neuron network: 103.3 ms; 108.3 with a search for every split; 106.5 with
+// the five launches). Bound: the latency of each launch's chain of dependent
+// loads, 5 to 10 us a launch while a step has few edges.
+__device__ __forceinline__ void pair_chunk(int n, int grid, int blk, int &c0, int &c1) {
+    const int per = ((n + grid - 1) / grid + kPairItems - 1) / kPairItems * kPairItems;
+    c0 = min(n, blk * per);
     c1 = min(n, c0 + per);
 }
 
-// Pass 1: owners of each chunk (SELCNT), from one coalesced read of the
-// records (a slot whose fresh record names a larger slot). It also empties the
-// previous step's table, which no kernel reads any more, for the next step.
-__global__ __launch_bounds__(kThreads) void k_hpair_count(Bufs b, StepGeom g) {
-    __shared__ int s_w[kThreads / 64];
-    // this step's split must not have failed its pairing (else the exact pass redoes it)
-    if (b.CTR[CTR_FLAGS] || b.CTR[CTR_PFAIL] <= g.step) return;
-    const int S = b.CTR[CTR_S], nslots = S * g.P;
-    int c0, c1;
-    pair_chunk(nslots, c0, c1);
-    if (g.HTo) {
-        const uint32_t clear_n = (uint32_t)b.CTR[CTR_TUSED + (g.par ^ 1)];
-        for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < clear_n; i += gridDim.x * kThreads) g.HTo[i] = 0ull;
-    }
-    int cnt = 0;
-    for (int u = c0 + (int)threadIdx.x; u < c1; u += kThreads) cnt += slot_partner(b, g, u, nslots) > u;
-    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = cnt;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int t = 0;
-        for (int w = 0; w < kThreads / 64; ++w) t += s_w[w];
-        b.SELCNT[blockIdx.x] = t;
-    }
+// slot u's record names a larger slot of this step
+__device__ __forceinline__ int owns(uint64_t r, int u, int step, int nslots) {
+    const int p1 = (int)(uint32_t)r;
+    return (uint32_t)(r >> 32) == (uint32_t)(step + 1) && p1 > u + 1 && p1 <= nslots;
 }
 
-// Pass 2: every slot's record checked; owners in slot order append their
-// intersecting edges.
-__global__ __launch_bounds__(kThreads) void k_hpair_emit(Bufs b, StepGeom g) {
-    __shared__ int s_w[kThreads / 64];
-    __shared__ int s_base;
-    if (b.CTR[CTR_FLAGS] || b.CTR[CTR_PFAIL] <= g.step) return;
-    const int S = b.CTR[CTR_S], nslots = S * g.P;
-    const int V0 = b.CTR[CTR_V + g.par], E0 = b.CTR[CTR_E + g.par], E1 = E0 + S;
+// the workgroup's share of emptying the previous step's table, which no kernel
+// reads any more, for the next step
+__device__ __forceinline__ void clear_table(const Bufs &b, const StepGeom &g) {
+    if (!g.HTo) return;
+    const uint32_t clear_n = (uint32_t)b.CTR[CTR_TUSED + (g.par ^ 1)];
+    for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < clear_n; i += gridDim.x * kThreads) g.HTo[i] = 0ull;
+}
+
+// Sum over the workgroup (every thread gets it); s_w: one int per wave.
+__device__ __forceinline__ int block_sum(int x, int *s_w) {
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    __syncthreads();  // s_w has been read
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = x;
+    __syncthreads();
+    int t = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) t += s_w[w];
+    return t;
+}
+
+// Rank of this thread among the workgroup's threads with `hit`, and their number.
+__device__ __forceinline__ int block_rank(bool hit, int &total, int *s_w) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t m = __ballot(hit);
+    __syncthreads();  // s_w has been read
+    if (lane == 0) s_w[wave] = __popcll(m);
+    __syncthreads();
+    int off = __popcll(m & ((1ull << lane) - 1ull));
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) {
+        const int x = s_w[w];
+        if (w < wave) off += x;
+        total += x;
+    }
+    return off;
+}
+
+// Chunk blk of nb of the edges there after the split: those that split at
+// neuron g.next. PACK: their ids to SPLX and their number to SELCNT, for
+// pack_chunk; else entries of the split list and its table.
+__device__ __forceinline__ void scan_range(int E1, int blk, int nb, int &c0, int &c1) {
+    const int per = ((E1 + nb - 1) / nb + kScanItems - 1) / kScanItems * kScanItems;
+    c0 = min(E1, blk * per);
+    c1 = min(E1, c0 + per);
+}
+
+template <bool PACK>
+__device__ __forceinline__ void scan_chunk(const Bufs &b, const StepGeom &g, int E1, int blk, int nb, int *s_w) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     int c0, c1;
-    pair_chunk(nslots, c0, c1);
+    scan_range(E1, blk, nb, c0, c1);
+    int run = c0;
+    // the next tile's bytes are loaded before this tile's scan, so that their
+    // latency hides behind it (raw words carried, compared at the next round)
+    int nbase = c0 + t * kScanItems;
+    uint4 ra = make_uint4(0, 0, 0, 0), rc = ra;
+    if (nbase + kScanItems <= c1) load32b(b.NX8, nbase, ra, rc);
+    for (int tb = c0; tb < c1; tb += kScanTile) {
+        const int base = nbase;
+        uint32_t hit = base < c1 ? match32b_raw(b.NX8, base, c1, (uint8_t)g.next, ra, rc) : 0u;
+        nbase = base + kScanTile;
+        if (nbase + kScanItems <= c1) load32b(b.NX8, nbase, ra, rc);
+        const int cnt = __popc(hit);
+        int incl = cnt;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        __syncthreads();  // s_w reuse
+        if (lane == 63) s_w[wave] = incl;
+        __syncthreads();
+        int wave_off = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) {
+            const int ws = s_w[w];
+            if (w < wave) wave_off += ws;
+            total += ws;
+        }
+        int pos = run + wave_off + incl - cnt;
+        while (hit) {
+            const int e = base + __builtin_ctz(hit);
+            hit &= hit - 1;
+            if (PACK) {
+                b.SPLX[pos++] = e;
+            } else {
+                const int2 ab = b.EDG[e];
+                b.SPLE[pos++] = make_int4(e, ab.x, ab.y, 0);
+            }
+        }
+        run += total;
+    }
+    if (t != 0) return;
+    if (PACK) b.SELCNT[kSelBlocks + blk] = run - c0;
+    else b.SELTAB[blk] = make_int2(c0, run - c0);
+}
+
+// The matches of the scan's chunk blk of nb to their places in the split list:
+// its first chunk, as one.
+__device__ __forceinline__ void pack_chunk(const Bufs &b, int E1, int blk, int nb, int *s_w) {
+    const int t = threadIdx.x;
+    const int *cnt = b.SELCNT + kSelBlocks;
+    int c0, c1;
+    scan_range(E1, blk, nb, c0, c1);
+    // the first round of entries is loaded while the chunk's place is summed
+    const int n = cnt[blk];
+    int e0 = 0;
+    int2 ab0 = make_int2(0, 0);
+    if (t < n) {
+        e0 = b.SPLX[c0 + t];
+        ab0 = b.EDG[e0];
+    }
+    int before = 0;
+    for (int i = t; i < blk; i += kThreads) before += cnt[i];
+    const int base = block_sum(before, s_w);
+    if (t < n) b.SPLE[base + t] = make_int4(e0, ab0.x, ab0.y, 0);
+    for (int i = t + kThreads; i < n; i += kThreads) {
+        const int e = b.SPLX[c0 + i];
+        const int2 ab = b.EDG[e];
+        b.SPLE[base + i] = make_int4(e, ab.x, ab.y, 0);
+    }
+    if (t == 0 && blk == nb - 1) b.SELTAB[0] = make_int2(0, base + n);
+}
+
+// Chunk blk of np of the key slots; the owners before it are counted here
+// (RECOUNT) or summed from the first pass's counts. nscan: the chunks of the
+// scan, before the emission's in the next step's list.
+template <bool RECOUNT>
+__device__ __forceinline__ void emit_chunk(const Bufs &b, const StepGeom &g, int V0, int E0, int S, int blk, int np,
+                                           int nscan, int *s_w) {
+    const int nslots = S * g.P, E1 = E0 + S, t = threadIdx.x;
+    int c0, c1;
+    pair_chunk(nslots, np, blk, c0, c1);
     // one slot per thread: an owner's edge is a chain of dependent row loads,
     // so owners are spread over as many threads as possible. A slot's record,
     // its partner's, and its row words from the neuron on (where an owner's
@@ -938,53 +1119,114 @@ __global__ __launch_bounds__(kThreads) void k_hpair_emit(Bufs b, StepGeom g) {
         if (partner >= 0 ? slot_partner(b, g, partner, nslots) != u : b.PINFO[u] != kNoInfo)
             raise_pair_flag(b.CTR, FLAG_RUN, g.step);
     };
-    load_slot(c0 + t);  // in flight while the chunk's offset is summed
-    int pre_cnt = 0;
-    for (int i = t; i < (int)blockIdx.x; i += kThreads) pre_cnt += b.SELCNT[i];
-    for (int o = 32; o > 0; o >>= 1) pre_cnt += __shfl_xor(pre_cnt, o, 64);
-    if (lane == 0) s_w[wave] = pre_cnt;
-    __syncthreads();
+    load_slot(c0 + t);  // in flight while the owners before the chunk are counted
+    int before = 0;
+    if (RECOUNT) {
+        // (chunks start at multiples of kPairItems: two records per load)
+        const ulonglong2 *rec = reinterpret_cast<const ulonglong2 *>(b.PART);
+#pragma unroll 4
+        for (int u = 2 * t; u < c0; u += 2 * kThreads) {
+            const ulonglong2 r = rec[u >> 1];
+            before += owns(r.x, u, g.step, nslots) + owns(r.y, u + 1, g.step, nslots);
+        }
+    } else {
+        for (int i = t; i < blk; i += kThreads) before += b.SELCNT[i];
+    }
+    const int first = block_sum(before, s_w);
+    int run = first, listed = 0;
+    for (int tb = c0; tb < c1; tb += kThreads) {
+        const int u = tb + t;
+        if (tb != c0) load_slot(u);
+        const bool own = partner > u;
+        int total;
+        const int pos = E1 + run + block_rank(own, total, s_w);
+        int col = kNoCol;
+        if (own) col = emit_pair(b, g, V0, nslots, u, partner, (size_t)pos, false, g.verify != 0, pre);
+        run += total;
+        if (g.next >= 0) {
+            const bool hit = own && col == g.next;
+            const int at = block_rank(hit, total, s_w);
+            if (hit)
+                b.SPLE[E1 + first + listed + at] = make_int4(pos, V0 + u / g.P, V0 + partner / g.P, 0);
+            listed += total;
+        }
+    }
     if (t == 0) {
-        int x = 0;
-        for (int w = 0; w < kThreads / 64; ++w) x += s_w[w];
-        s_base = x;
-        if (blockIdx.x == gridDim.x - 1) {
+        if (g.next >= 0) b.SELTAB[nscan + blk] = make_int2(E1 + first, listed);
+        if (blk == np - 1) {
             // the next step's counts, and this step's log entry
-            const int En = E1 + x + b.SELCNT[blockIdx.x];
+            const int En = E1 + run;
             b.CTR[CTR_E + (g.par ^ 1)] = En;
             if (g.HT) b.CTR[CTR_TUSED + g.par] = (uint32_t)nslots <= kMaxHashSlots ? (int)table_size(nslots) : 0;
             if (S > b.CTR[CTR_SMAX]) b.CTR[CTR_SMAX] = S;
             if (b.REC) b.REC[g.step] = StepRec{V0, E0, S, En};
         }
     }
-    __syncthreads();
-    int run = s_base;
-    for (int tb = c0; tb < c1; tb += kThreads) {
-        const int u = tb + t;
-        if (tb != c0) load_slot(u);
-        const bool own = partner > u;
-        const uint64_t m = __ballot(own);
-        __syncthreads();  // s_w of the previous round has been read
-        if (lane == 0) s_w[wave] = __popcll(m);
-        __syncthreads();
-        int wave_off = 0, total = 0;
-#pragma unroll
-        for (int w = 0; w < kThreads / 64; ++w) {
-            const int ws = s_w[w];
-            if (w < wave) wave_off += ws;
-            total += ws;
-        }
-        if (own) {
-            const int pos = run + wave_off + __popcll(m & ((1ull << lane) - 1ull));
-            emit_pair(b, g, V0, nslots, u, partner, (size_t)E1 + pos, false, g.verify != 0, pre);
-        }
-        run += total;
-    }
 }
 
-void launch_hash_pair(const Bufs &b, const StepGeom &g, int grid, hipStream_t st) {
-    hipLaunchKernelGGL(k_hpair_count, dim3(grid), dim3(kThreads), 0, st, b, g);
-    hipLaunchKernelGGL(k_hpair_emit, dim3(grid), dim3(kThreads), 0, st, b, g);
+// this step's split must not have failed its pairing (else the exact pass redoes it)
+__device__ __forceinline__ bool pair_blocked(const Bufs &b, const StepGeom &g) {
+    return b.CTR[CTR_FLAGS] || b.CTR[CTR_PFAIL] <= g.step;
+}
+
+// Small steps: np emission workgroups, which count the owners before their
+// chunks themselves, then the scan's.
+__global__ __launch_bounds__(kThreads) void k_pair_scan(Bufs b, StepGeom g, int np) {
+    __shared__ int s_w[kThreads / 64];
+    if (pair_blocked(b, g)) return;
+    const int V0 = b.CTR[CTR_V + g.par], E0 = b.CTR[CTR_E + g.par], S = b.CTR[CTR_S];
+    clear_table(b, g);
+    const int nscan = (int)gridDim.x - np;
+    if ((int)blockIdx.x < np) emit_chunk<true>(b, g, V0, E0, S, blockIdx.x, np, nscan, s_w);
+    else scan_chunk<false>(b, g, E0 + S, blockIdx.x - np, nscan, s_w);
+}
+
+// Large steps, first launch: the owners of each of np chunks of the slots
+// (SELCNT) from one coalesced read of the records, and the scan beside it.
+__global__ __launch_bounds__(kThreads) void k_count_scan(Bufs b, StepGeom g, int np) {
+    __shared__ int s_w[kThreads / 64];
+    if (pair_blocked(b, g)) return;
+    const int E0 = b.CTR[CTR_E + g.par], S = b.CTR[CTR_S], nslots = S * g.P;
+    clear_table(b, g);
+    if ((int)blockIdx.x >= np) {
+        scan_chunk<true>(b, g, E0 + S, blockIdx.x - np, (int)gridDim.x - np, s_w);
+        return;
+    }
+    int c0, c1;
+    pair_chunk(nslots, np, blockIdx.x, c0, c1);
+    int cnt = 0;
+    for (int u = c0 + (int)threadIdx.x; u < c1; u += kThreads) cnt += owns(b.PART[u], u, g.step, nslots);
+    cnt = block_sum(cnt, s_w);
+    if (threadIdx.x == 0) b.SELCNT[blockIdx.x] = cnt;
+}
+
+// second launch: the emission, and the scan's matches packed beside it
+__global__ __launch_bounds__(kThreads) void k_pair_emit(Bufs b, StepGeom g, int np) {
+    __shared__ int s_w[kThreads / 64];
+    if (pair_blocked(b, g)) return;
+    const int V0 = b.CTR[CTR_V + g.par], E0 = b.CTR[CTR_E + g.par], S = b.CTR[CTR_S];
+    if ((int)blockIdx.x < np) emit_chunk<false>(b, g, V0, E0, S, blockIdx.x, np, 1, s_w);
+    else pack_chunk(b, E0 + S, blockIdx.x - np, (int)gridDim.x - np, s_w);
+}
+
+// Steps of up to this many key slots count their owners in the emission itself:
+// the last workgroup then reads at most 128 KB of records, beside its own
+// slots' loads. Over 3-64-64-64-1 (up to 26K slots a step) the one launch takes
+// 7.4 us a step where the two take 11; with twice this limit the extraction
+// takes 4.54 ms, not 4.49.
+constexpr int64_t kRecountSlots = 16384;
+
+int launch_hash_pair(const Bufs &b, const StepGeom &g, int64_t slots, int64_t edges, bool full, hipStream_t st) {
+    const int np = full ? kSelBlocks : clamp_grid((slots + 255) / 256, 1);
+    const int nscan = g.next < 0 ? 0 : full ? kSelBlocks : clamp_grid((edges + 2047) / 2048, 1);
+    static_assert(2 * kSelBlocks <= kListMax && 2 * kSelBlocks <= kNextBlocks, "chunks of both kinds fit the tables");
+    if (!full && slots <= kRecountSlots) {
+        hipLaunchKernelGGL(k_pair_scan, dim3(np + nscan), dim3(kThreads), 0, st, b, g, np);
+        return g.next < 0 ? 0 : nscan + np;
+    }
+    hipLaunchKernelGGL(k_count_scan, dim3(np + nscan), dim3(kThreads), 0, st, b, g, np);
+    hipLaunchKernelGGL(k_pair_emit, dim3(np + nscan), dim3(kThreads), 0, st, b, g, np);
+    return g.next < 0 ? 0 : 1 + np;
 }
 
 // ------------------------------------- step 5c, the exact pass of a step
@@ -1091,7 +1333,7 @@ void launch_fill64(uint64_t *p, size_t n, uint64_t v, hipStream_t st) {
     hipLaunchKernelGGL(k_fill64, dim3(grid), dim3(kThreads), 0, st, p, n, v);
 }
 
-void launch_exact_pair(const Bufs &b, const StepGeom &g, int nslots, int grid, hipStream_t st) {
+void launch_exact_pair(const Bufs &b, StepGeom g, int nslots, bool full, hipStream_t st) {
     if (nslots > 0) {
         const int kg = std::min(8192, (nslots + kThreads - 1) / kThreads);
         hipLaunchKernelGGL(k_exact_keys, dim3(kg), dim3(kThreads), 0, st, b, g, nslots);
@@ -1100,7 +1342,8 @@ void launch_exact_pair(const Bufs &b, const StepGeom &g, int nslots, int grid, h
         launch_sort64(b, nslots, st, &keys, &vals);
         hipLaunchKernelGGL(k_exact_group, dim3(kg), dim3(kThreads), 0, st, b, g, nslots, keys, vals);
     }
-    launch_hash_pair(b, g, grid, st);
+    g.next = -1;
+    launch_hash_pair(b, g, nslots, 0, full, st);
 }
 
 }  // namespace pcx

@@ -116,7 +116,8 @@ extern "C" int pcx_extract_into(const pcx_mlp *mlp, const double *lo, const doub
     auto layout = [&](Carve &c) {
         b.CTR = c.take<int>(CTR_COUNT);
         b.VALID = c.take<uint64_t>(Wd);
-        b.SELCNT = c.take<int>(kNextBlocks);
+        b.SELCNT = c.take<int>(kSelWords);
+        b.SELTAB = (int2 *)(b.SELCNT + kNextBlocks);
         b.REC = c.take<StepRec>(std::max(1, n_steps));
         b.Z = c.take<double>(Vcap * ZS);
         b.LW = c.take<uint64_t>(Vcap * 8);
@@ -212,6 +213,7 @@ extern "C" int pcx_extract_into(const pcx_mlp *mlp, const double *lo, const doub
         g.hkeep = ~0ull;
         g.fbits = 64;
         g.verify = o.verify_pairs ? 1 : 0;
+        g.next = j + 1 < g.Nl ? j + 1 : -1;
         g.Vcap = (int)Vcap;
         g.Ecap = (int)Ecap;
         g.Kcap = (int)std::min<size_t>(Kcap, INT32_MAX);
@@ -235,7 +237,7 @@ extern "C" int pcx_extract_into(const pcx_mlp *mlp, const double *lo, const doub
         if (nslots > (int64_t)Kcap) return fail(PCX_ERR_DEVICE, "internal error: key slots beyond the storage");
         int r;
         if ((r = put(CTR_PFLAGS, 0)) || (r = put(CTR_PFAIL, 0x7fffffff))) return r;
-        launch_exact_pair(b, geom(lf, pf - step0[lf]), (int)nslots, pair_grid(nslots), st);
+        launch_exact_pair(b, geom(lf, pf - step0[lf]), (int)nslots, false, st);
         HIPCHK(hipGetLastError());
         if ((r = drain())) return r;
         if (ctr[CTR_FLAGS] || ctr[CTR_PFLAGS]) return degenerate_message(ctr[CTR_FLAGS] | ctr[CTR_PFLAGS]);
@@ -247,9 +249,11 @@ extern "C" int pcx_extract_into(const pcx_mlp *mlp, const double *lo, const doub
     constexpr int kAhead = 8;
     int64_t V = V0, E = E0, Sgrid = 64;
     int l = 0, j = 0;
+    int nlist = 0;  // chunks of the next step's split list that the last pairing wrote (0: none to be used)
     bool started = false;
     while (true) {
         if (!started) {
+            nlist = 0;
             if ((rc = drain())) return rc;
             int f;
             if ((rc = recover(f))) return rc;
@@ -287,6 +291,7 @@ extern "C" int pcx_extract_into(const pcx_mlp *mlp, const double *lo, const doub
             if (f >= 0) {
                 if (f < step0[l] || f > s) return fail(PCX_ERR_DEVICE, "internal error: bad failing step");
                 j = f - step0[l];
+                nlist = 0;
                 continue;
             }
             Sgrid = std::max<int64_t>(Sgrid, ctr[CTR_SMAX] + ctr[CTR_SMAX] / 4 + 64);
@@ -296,11 +301,14 @@ extern "C" int pcx_extract_into(const pcx_mlp *mlp, const double *lo, const doub
         if (j == 0) {
             launch_next_all(b, (int)V, Wd, lw[l], lw[l + 1], (int)E, par, s, st);
             launch_gather(b, (int)E, par, s, st);
-        } else {
+            nlist = 1;
+        } else if (nlist == 0) {
             launch_select(b, (uint16_t)j, par, s, select_grid(E), st);
+            nlist = 1;
         }
+        g.nlist = nlist;
         launch_split(b, g, split_blocks((int)std::min<int64_t>(Sgrid, INT32_MAX), N), st);
-        launch_hash_pair(b, g, pair_grid(Sgrid * P), st);
+        nlist = launch_hash_pair(b, g, Sgrid * P, E, false, st);
         HIPCHK(hipGetLastError());
         ++j;
     }
