@@ -346,7 +346,7 @@ int future_signs(Extraction &x, const pcx_mlp *mlp, int l, int nsub, int64_t V, 
             bb.Z = (double *)q[m & 1];
             bb.SG = x.b.SG + (size_t)c0 * Wd;
             launch_gemm(bb, ZS, src, ZS, 1, n, mlp->widths[m], mlp->widths[m + 1], mlp->Wt[m], mlp->b[m], Wd, lw[m],
-                        x.st);
+                        mlp->finite[m], x.st);
             src = bb.Z;
         }
     }
@@ -437,8 +437,14 @@ int pcx_mlp_create(int32_t n_layers, const int32_t *widths, const double *const 
             return fail(PCX_ERR_INVALID, "NULL weight or bias pointer");
         }
         tmp.resize((size_t)nin * nout);
+        bool finite = true;
         for (int i = 0; i < nout; ++i)
-            for (int k = 0; k < nin; ++k) tmp[(size_t)k * nout + i] = W[l][(size_t)i * nin + k];
+            for (int k = 0; k < nin; ++k) {
+                const double w = W[l][(size_t)i * nin + k];
+                finite = finite && std::isfinite(w);
+                tmp[(size_t)k * nout + i] = w;
+            }
+        m->finite.push_back(finite);
         double *dw = nullptr, *db = nullptr, *dr = nullptr;
         bool ok;
         {
@@ -563,6 +569,16 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
         for (int c = 0; c < mlp->widths[l + 1]; ++c) valid[lw[l] + (c >> 5)] |= 1ull << (2 * (c & 31));
 
     const bool box = dom.lo != nullptr;
+    std::vector<double> dlo(dom.lo, dom.lo + (box ? D : 0)), dhi(dom.hi, dom.hi + (box ? D : 0));
+    if (!box) {  // the bounding box of the domain's vertices
+        dlo.assign(dom.X0.begin(), dom.X0.begin() + D);
+        dhi = dlo;
+        for (size_t i = 0; i < dom.X0.size(); ++i) {
+            dlo[i % D] = std::min(dlo[i % D], dom.X0[i]);
+            dhi[i % D] = std::max(dhi[i % D], dom.X0[i]);
+        }
+    }
+    const EvalGrid egrid = eval_grid(D, dlo.data(), dhi.data());
     const size_t V0 = box ? (size_t)1 << D : dom.W0.size(), E0 = box ? (size_t)D << (D - 1) : dom.E0.size();
     if ((rc = x.attach_host())) return rc;
     if ((shortcuts & kShortcutGraph) && dom.lo) {
@@ -844,9 +860,12 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
                 x.b.LW = (uint64_t *)q;
             }
             // step 1 for the whole layer: pre-activations at every vertex
+            // (the split list's storage, free here, is the evaluation's scratch)
+            const EvalGrid *eg = x.Ecap >= (size_t)V ? &egrid : nullptr;
+            const bool fin = mlp->finite[l];
             if ((rc = x.mark(PCX_K_GEMM, true))) return rc;
             if (l == 0) {
-                launch_gemm(x.b, ZS, x.b.X, D, 0, (int)V, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], st);
+                launch_gemm(x.b, ZS, x.b.X, D, 0, (int)V, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], fin, st);
             } else if (x.tape) {
                 // keep the previous layer's rows: evaluate into a fresh buffer
                 double *prev = x.b.Z;
@@ -854,9 +873,9 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
                 if ((rc = x.arena.alloc(&q, x.Vcap * (size_t)ZS * sizeof(double)))) return rc;
                 tapeZ.push_back(prev);
                 x.b.Z = (double *)q;
-                launch_gemm(x.b, ZS, prev, ZS, 1, (int)V, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], st);
+                launch_gemm(x.b, ZS, prev, ZS, 1, (int)V, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], fin, st, eg);
             } else {
-                launch_gemm(x.b, ZS, x.b.Z, ZS, 1, (int)V, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], st);
+                launch_gemm(x.b, ZS, x.b.Z, ZS, 1, (int)V, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], fin, st, eg);
             }
             if ((rc = x.mark(PCX_K_GEMM, false))) return rc;
             if (x.prune) {

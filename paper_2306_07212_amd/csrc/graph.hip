@@ -155,6 +155,7 @@ int build(const pcx_mlp *mlp, const GraphLog &lg, GraphEntry &ge, hipStream_t cs
     if (!gate.owns_lock()) return kGraphBusy;
     HIPCHK(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
     const int V0 = 1 << D, E0 = D << (D - 1);
+    const EvalGrid egrid = eval_grid(D, lg.lo.data(), lg.hi.data());
     launch_ctr_init(b.CTR, V0, E0, cs);
     launch_fill64(b.PART, Kcap, 0ull, cs);
     launch_fill64(reinterpret_cast<uint64_t *>(HT[0]), Tcap, 0ull, cs);
@@ -164,8 +165,9 @@ int build(const pcx_mlp *mlp, const GraphLog &lg, GraphEntry &ge, hipStream_t cs
         const int N = mlp->widths[l + 1], K = mlp->widths[l];
         const int64_t *sl = &lg.steps[(size_t)step0[l] * 4];
         const int Vl = (int)sl[0], El = (int)sl[1];
-        if (l == 0) launch_gemm(b, ZS, b.X, D, 0, Vl, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], cs);
-        else launch_gemm(b, ZS, b.Z, ZS, 1, Vl, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], cs);
+        if (l == 0) launch_gemm(b, ZS, b.X, D, 0, Vl, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], mlp->finite[l], cs);
+        else launch_gemm(b, ZS, b.Z, ZS, 1, Vl, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], mlp->finite[l], cs,
+                         Ecap >= (size_t)Vl ? &egrid : nullptr);
         int nlist = 1;
         for (int j = 0; j < N; ++j) {
             const int s = step0[l] + j, par = s & 1;

@@ -55,6 +55,7 @@ struct pcx_mlp {
     std::vector<double *> Wt;  // device, layer l: [N_{l-1}][N_l] (transposed for coalesced GEMM reads)
     std::vector<double *> Wr;  // device, layer l: [N_l][N_{l-1}] as given (backward pass)
     std::vector<double *> b;   // device, [N_l]
+    std::vector<char> finite;  // layer l: every weight is finite (0 * w = 0)
     std::atomic<int64_t> hintV{0}, hintE{0}, hintS{0};  // sizes seen by earlier extractions (capacity hints)
     pcx::GraphCache *gcache = nullptr;  // the last extraction's step log and its captured graph (graph.hip)
 };
@@ -86,6 +87,18 @@ struct pcx_complex {
 
 
 namespace pcx {
+// The grid by which evaluations order the rows of a complex inside [lo, hi]
+// (D entries each): the cells' bits shared out over the axes.
+inline EvalGrid eval_grid(int D, const double *lo, const double *hi) {
+    EvalGrid g{};
+    g.D = D;
+    for (int d = 0; d < D; ++d) {
+        g.bits[d] = kBinBits / D + (d < kBinBits % D ? 1 : 0);
+        g.lo[d] = lo[d];
+        g.scale[d] = (double)(1 << g.bits[d]) / (hi[d] - lo[d]);
+    }
+    return g;
+}
 // A graph capture (graph.hip) on one thread must not overlap this library's
 // device allocations and frees on other threads: those take this gate shared,
 // a capture takes it exclusively (and is skipped when it cannot have it).

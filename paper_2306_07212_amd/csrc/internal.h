@@ -139,10 +139,25 @@ struct Bufs {
                       // layer-start scan (written by the evaluation when set; else null)
 };
 
+// The grid over the domain's bounding box by which an evaluation orders its
+// rows: 2^bits[d] cells along axis d, 2^kBinBits in all.
+constexpr int kBinBits = 12;
+constexpr int kBinRows = 32768;  // rows, and products, from which an evaluation orders them
+constexpr int64_t kBinWork = (int64_t)1 << 31;
+struct EvalGrid {
+    int D;
+    double lo[16], scale[16];
+    int bits[16];
+};
+
 // launchers (kernels.hip)
 void launch_init_box(const Bufs &b, int D, int Wd, const double *lo, const double *hi, hipStream_t st);
+// finite: every weight is. grid (null: rows as they are): b.X holds the rows'
+// coordinates, and large evaluations may take them in spatial order; SPLX and
+// SPLE are scratch for that.
 void launch_gemm(const Bufs &b, int ZS, const double *in, int in_stride, int relu, int V, int K, int N,
-                 const double *Wt, const double *bias, int Wd, int lw0, hipStream_t st);
+                 const double *Wt, const double *bias, int Wd, int lw0, bool finite, hipStream_t st,
+                 const EvalGrid *grid = nullptr);
 // first crossing of every edge in the layer (NX8; the edge count comes from
 // CTR_E[par]), and the ordered compaction of the edges that cross the layer's
 // first neuron (the first pass of that step's split list: SPLX, SELCNT)

@@ -135,182 +135,344 @@ __global__ __launch_bounds__(kGemvRows) void k_gemv(Bufs b, int ZS, const double
     if (zero) raise_flag(b.CTR, FLAG_ZERO_SIGN);
 }
 
-// The same evaluation on the matrix cores, for wide layers (N > 128, K >= 16).
-// Wave w owns columns [64 (w%4), +64) of the row band w/4 as RT x 4 tiles of
-// the FP64 16x16x4 MFMA (lane l of a tile holds rows l/16 + 4i, column l%16,
-// i = 0..3). A chain of these MFMAs rounds exactly like the sequential fma
-// chain of k_gemm, so both kernels give identical bits. K advances in chunks
-// of MK staged through LDS (h k-major, W^T row-major); the next chunk's global
-// loads are in flight while the current chunk's MFMAs run, and with DB the LDS
-// is double-buffered (one barrier per chunk). In place as above: a workgroup
-// reads all its rows before the epilogue writes them. Launched with 8 waves
-// of 2 x 4 tiles (64 rows per workgroup, 4 waves per SIMD), MK = 8.
-constexpr int kMPad = 2;
+// ---- rows of an evaluation in spatial order
+//
+// Vertices that lie close together share most of the previous layer's dead
+// neurons (h = 0): in 64 neighbouring rows of the 768-neuron network about 45%
+// of the columns are zero in all of them, and the matrix-core kernel below
+// skips those. The rows are binned by a grid of 2^12 cells over the domain's
+// bounding box (12 bits of the coordinates shared out over the axes); the order
+// inside a bin does not matter, since every row's result is its own. Bound:
+// one read of the coordinates a pass, two passes and 4 B a row written
+// (0.35 ms over the 768-neuron network's two layers, 14.2M rows). In their own
+// order 64 rows there leave 78 to 90% of the columns, by this grid 55 to 57%,
+// by one of 2^15 cells 54 to 55%. From kBinRows rows and kBinWork products on:
+// below, the four launches cost more than they save.
+constexpr int kBins = 4096, kBinThreads = 1024;
+
+__device__ __forceinline__ int bin_of(const double *__restrict__ x, const EvalGrid &g, int D) {
+    int key = 0;
+    for (int d = 0; d < D; ++d) {
+        const int n = 1 << g.bits[d];
+        const int i = (int)((x[d] - g.lo[d]) * g.scale[d]);  // (out of range, also NaN: an end cell)
+        key = key * n + min(max(i, 0), n - 1);
+    }
+    return key;
+}
+
+// rows of workgroup blk
+__device__ __forceinline__ void bin_rows(int V, int &v0, int &v1) {
+    const int per = (V + (int)gridDim.x - 1) / (int)gridDim.x;
+    v0 = min(V, (int)blockIdx.x * per);
+    v1 = min(V, v0 + per);
+}
+
+__global__ __launch_bounds__(kBinThreads) void k_bin_count(const double *__restrict__ X, EvalGrid g, int D, int V,
+                                                           int *__restrict__ cnt) {
+    __shared__ int h[kBins];
+    const int t = threadIdx.x;
+    for (int i = t; i < kBins; i += kBinThreads) h[i] = 0;
+    __syncthreads();
+    int v0, v1;
+    bin_rows(V, v0, v1);
+    for (int v = v0 + t; v < v1; v += kBinThreads) atomicAdd(&h[bin_of(X + (size_t)v * D, g, D)], 1);
+    __syncthreads();
+    for (int i = t; i < kBins; i += kBinThreads)
+        if (h[i]) atomicAdd(&cnt[i], h[i]);
+}
+
+// counts -> first places (exclusive prefix sums), by one workgroup
+__global__ __launch_bounds__(kBinThreads) void k_bin_scan(int *cnt) {
+    __shared__ int s_w[kBinThreads / 64];
+    constexpr int per = kBins / kBinThreads;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    int x[per], mine = 0;
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+        x[i] = cnt[t * per + i];
+        mine += x[i];
+    }
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    if (lane == 63) s_w[wave] = incl;
+    __syncthreads();
+    int run = incl - mine;
+    for (int w = 0; w < wave; ++w) run += s_w[w];
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+        cnt[t * per + i] = run;
+        run += x[i];
+    }
+}
+
+__global__ __launch_bounds__(kBinThreads) void k_bin_scatter(const double *__restrict__ X, EvalGrid g, int D, int V,
+                                                             int *__restrict__ next, int *__restrict__ perm) {
+    __shared__ int h[kBins];
+    const int t = threadIdx.x;
+    for (int i = t; i < kBins; i += kBinThreads) h[i] = 0;
+    __syncthreads();
+    int v0, v1;
+    bin_rows(V, v0, v1);
+    for (int v = v0 + t; v < v1; v += kBinThreads) atomicAdd(&h[bin_of(X + (size_t)v * D, g, D)], 1);
+    __syncthreads();
+    for (int i = t; i < kBins; i += kBinThreads)
+        if (h[i]) h[i] = atomicAdd(&next[i], h[i]);  // this workgroup's places in the bin
+    __syncthreads();
+    for (int v = v0 + t; v < v1; v += kBinThreads) perm[atomicAdd(&h[bin_of(X + (size_t)v * D, g, D)], 1)] = v;
+}
+
+// The same evaluation on the matrix cores (N > kGemvMaxN, finite weights). A
+// workgroup takes 32 rows; its 4 waves are CW blocks of 16 CT columns and 4 / CW
+// bands of 16 RT rows, a wave RT x CT tiles of the FP64 16x16x4 MFMA (lane l of a
+// tile holds rows l/16 + 4i, column l%16, i = 0..3). A chain of these MFMAs
+// rounds exactly like the sequential fma chain of k_gemm, so both kernels give
+// identical bits.
+//
+// The rows are read once, all loads in flight together (nothing looks at a value
+// before the last is issued), and the inputs (ReLU applied) that are not zero in
+// all 32 rows go to LDS, so that the product loop has no barrier and skips the
+// other columns: adding 0 * w leaves a sum as it is (w finite, the sum started
+// at +0), so the bits are the same. With the rows in spatial order (perm) 45% of
+// the columns of the 768-neuron network fall out, in their own order 10 to 20%.
+// A wave reads its weights straight from the L2, SLOTS k-steps ahead. In place
+// as above: a workgroup reads all its rows before the epilogue writes them.
+//
+// Bound: the rows' traffic (4.6 KB a row at K = N = 256) and the matrix cores,
+// about equal once 45% of the columns are out, so 39 KB of LDS (KSEG columns at
+// a time, mostly all of them) lets four workgroups of a CU take turns at both.
+// 2M rows of 256, 115 columns out: 3.35 ms; 3.53 with two workgroups of 64 rows;
+// 2.45 without the products, about 2.2 for them alone. The 768-neuron network's
+// two layers: 23.5 ms, 38.1 with every column in barrier-separated chunks of 8
+// whose ReLU waited for each load.
+constexpr int kEvalThreads = 256, kEvalRows = 32;
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
-// RT: 16-row tiles per wave; WAVES: waves per workgroup, 4 per 64-row band of
-// column blocks (wave w: columns [64 (w%4), +64), row band w/4).
-template <int MK, int RT, int WAVES, int MINW, bool DB, int PF>
-__global__ __launch_bounds__(64 * WAVES, MINW) void k_gemm_mfma(Bufs b, int ZS, const double *in, int in_stride,
-                                                                int relu, int V, int K, int N,
-                                                                const double *__restrict__ Wt,
-                                                                const double *__restrict__ bias, int Wd, int lw0) {
-    constexpr int T = 64 * WAVES;
-    constexpr int ROWS = (WAVES / 4) * RT * 16;
-    constexpr int APT = ROWS * MK / T;  // h values staged per thread
-    constexpr int WPT = MK * kMaxWidth / T;  // W^T values staged per thread
-    static_assert(APT >= 1 && MK % APT == 0 && WPT >= 1, "staging map");
-    constexpr int NB = DB ? 2 : 1;
-    __shared__ double as[NB][MK][ROWS + kMPad];
-    __shared__ double ws[NB][MK][kMaxWidth + kMPad];
-    const int t = threadIdx.x, l = t & 63, w = t >> 6;
+template <int CW, int CT, int RT>
+__global__ __launch_bounds__(kEvalThreads, 4) void k_gemm_mfma(Bufs b, int ZS, const double *in, int in_stride,
+                                                               int relu, int V, int K, int N,
+                                                               const double *__restrict__ Wt,
+                                                               const double *__restrict__ bias, int Wd, int lw0,
+                                                               const int *__restrict__ perm) {
+    constexpr int ROWS = kEvalRows, WAVES = kEvalThreads / 64, SLOTS = 2;
+    static_assert((WAVES / CW) * 16 * RT == ROWS && CT % 2 == 0 && kEvalThreads == kMaxWidth, "wave layout");
+    constexpr int PITCH = 146;                  // 16 rows of a tile start 4 banks apart: no conflicts
+    constexpr int KSEG = PITCH / (4 * SLOTS) * (4 * SLOTS);
+    constexpr int RPW = ROWS / WAVES;           // rows staged by a wave
+    constexpr int CPL = kMaxWidth / 64;         // columns of a row staged by a lane
+    constexpr uint16_t kOut = 0xFFFF;           // a column that is zero in every row
+    __shared__ double as[ROWS][PITCH];
+    __shared__ uint32_t s_off[kMaxWidth + 8 * SLOTS];  // byte offset of each multiplied column's weights
+    __shared__ uint16_t s_idx[kMaxWidth];              // its place among the multiplied ones, by column
+    __shared__ uint8_t s_any[kMaxWidth];               // columns that are not zero in some row
+    __shared__ int s_row[ROWS];                        // the workgroup's rows (-1: none)
+    __shared__ int s_n[4];
+    const int t = threadIdx.x, l = t & 63, w = t >> 6, r = l & 15, q = l >> 4;
     const int v0 = blockIdx.x * ROWS;
-    // staging map: h row t / (MK/APT), k offsets APT (t % (MK/APT)) .. +APT-1;
-    // W^T rows WPT (t / 256) .. +WPT-1, column t % 256
-    const int ar = t / (MK / APT), ak = (t % (MK / APT)) * APT;
-    const int wc = t % kMaxWidth, wk = (t / kMaxWidth) * WPT;
-    const bool arow = v0 + ar < V;
-    const double *arow_p = in + (size_t)(v0 + ar) * in_stride;
-    double pa[PF][APT], pw[PF][WPT];  // PF chunks of staged loads in flight
-    auto fetch = [&](int k0, int slot) {
+    if (t < ROWS) s_row[t] = v0 + t >= V ? -1 : perm ? perm[v0 + t] : v0 + t;
+    s_any[t] = 0;
+    __syncthreads();
+    // wave w reads rows RPW w .. +RPW-1, a lane the columns l, l + 64, ...
+    double x[CPL][RPW];
+    const double *row[RPW];
 #pragma unroll
-        for (int i = 0; i < APT; ++i) {
-            double h = 0.0;
-            if (arow && k0 + ak + i < K) {
-                h = arow_p[k0 + ak + i];
-                if (relu) h = h > 0.0 ? h : 0.0;
-            }
-            pa[slot][i] = h;
-        }
+    for (int i = 0; i < RPW; ++i)
+        row[i] = in + (size_t)max(__builtin_amdgcn_readfirstlane(s_row[w * RPW + i]), 0) * in_stride;
 #pragma unroll
-        for (int i = 0; i < WPT; ++i)
-            pw[slot][i] = (k0 + wk + i < K && wc < N) ? Wt[(size_t)(k0 + wk + i) * N + wc] : 0.0;
+    for (int c = 0; c < CPL; ++c) {
+        if (c * 64 >= K) break;
+        const int k = min(c * 64 + l, K - 1);
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) x[c][i] = row[i][k];
+    }
+    auto value = [&](double v, int i) {  // input of row w * RPW + i
+        return (s_row[w * RPW + i] >= 0) & ((relu == 0) | (v > 0.0)) ? v : 0.0;
     };
-    dbl4 acc[RT][4];
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+        if (c * 64 >= K) break;
+        bool any = false;
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+            x[c][i] = value(x[c][i], i);
+            any |= !(x[c][i] == 0.0);
+        }
+        if (any && c * 64 + l < K) s_any[c * 64 + l] = 1;
+    }
+    __syncthreads();
+    {
+        const bool act = s_any[t];
+        const uint64_t m = __ballot(act);
+        if (l == 0) s_n[w] = __popcll(m);
+        __syncthreads();
+        int pos = __popcll(m & ((1ull << l) - 1ull));
+        for (int i = 0; i < w; ++i) pos += s_n[i];
+        s_idx[t] = act ? (uint16_t)pos : kOut;
+        if (act) s_off[pos] = (uint32_t)(t * N) * 8u;
+    }
+    const int KA = s_n[0] + s_n[1] + s_n[2] + s_n[3];  // columns to multiply
+    if (t < 8 * SLOTS) s_off[KA + t] = 0u;  // (weights that are there, for the loads past the end)
+    __syncthreads();
+    auto pad = [](int n) { return (n + 4 * SLOTS - 1) / (4 * SLOTS) * (4 * SLOTS); };
+    // the multiplied columns ks .. ks + KSEG - 1 to LDS, with zeros up to a whole round
+    auto zeros = [&](int kn) {
+        const int n = pad(kn) - kn;
+        if (t < ROWS * n) as[t / n][kn + t % n] = 0.0;  // (n < 8: at most 7 * ROWS threads)
+    };
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+        if (c * 64 >= K) break;
+        const int k = c * 64 + l, p = k < K ? s_idx[k] : kOut;
+        if (p < KSEG) {
+#pragma unroll
+            for (int i = 0; i < RPW; ++i) as[w * RPW + i][p] = x[c][i];
+        }
+    }
+    zeros(min(KSEG, KA));
+    const int col0 = (w % CW) * 16 * CT;
+    const int rb = (w / CW) * RT * 16;
+    uint32_t cb[CT];  // byte offset of this lane's columns in a row of W^T
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) cb[ct] = (uint32_t)min(col0 + ct * 16 + r, N - 1) * 8u;
+    const char *wbase = reinterpret_cast<const char *>(Wt);
+    double bw[SLOTS][CT];
+    auto load_w = [&](int k, int slot) {  // the weights of k-step k .. k+3
+        const uint32_t o = s_off[k + q];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) bw[slot][ct] = *reinterpret_cast<const double *>(wbase + (o + cb[ct]));
+    };
+    __syncthreads();
+    dbl4 acc[RT][CT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) acc[rt][ct] = dbl4{0.0, 0.0, 0.0, 0.0};
-    const int col0 = (w & 3) * 64;
-    const int rb = (w >> 2) * RT * 16;
-    const bool wave_live = col0 < N;
-    double bv[4];  // this lane's bias values, loaded before the main loop
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-        const int col = col0 + ct * 16 + (l & 15);
-        bv[ct] = col < N ? bias[col] : 0.0;
-    }
-    auto put = [&](int buf, int slot) {
-#pragma unroll
-        for (int i = 0; i < APT; ++i) as[buf][ak + i][ar] = pa[slot][i];
-#pragma unroll
-        for (int i = 0; i < WPT; ++i) ws[buf][wk + i][wc] = pw[slot][i];
-    };
-    auto compute = [&](int buf) {
-        if (!wave_live) return;
-        __builtin_amdgcn_s_setprio(1);  // MFMA issue ahead of the other waves' staging
-#pragma unroll
-        for (int kk = 0; kk < MK; kk += 4) {
-            double af[RT], bf[4];
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) af[rt] = as[buf][kk + (l >> 4)][rb + rt * 16 + (l & 15)];
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct) bf[ct] = ws[buf][kk + (l >> 4)][col0 + ct * 16 + (l & 15)];
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct)
-                    acc[rt][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[rt], bf[ct], acc[rt][ct], 0, 0, 0);
-        }
-        __builtin_amdgcn_s_setprio(0);
-    };
-#pragma unroll
-    for (int p = 0; p < PF; ++p)
-        if (p * MK < K) fetch(p * MK, p);
-    if (DB) {
-        // one barrier per chunk: compute from one buffer while the next chunk is stored into the other
-        put(0, 0);
-        __syncthreads();
-        int c = 0;
-        for (int k0 = 0; k0 < K; k0 += MK, ++c) {
-            const bool more = k0 + MK < K;
-            if (k0 + PF * MK < K) fetch(k0 + PF * MK, c % PF);
-            compute(c & 1);
-            if (more) put((c & 1) ^ 1, (c + 1) % PF);
-            __syncthreads();
-        }
-    } else {
-        int c = 0;
-        for (int k0 = 0; k0 < K; k0 += MK, ++c) {
-            __syncthreads();
-            put(0, c % PF);
-            __syncthreads();
-            if (k0 + PF * MK < K) fetch(k0 + PF * MK, c % PF);
-            compute(0);
-        }
-    }
-    if (!wave_live) return;
-    // epilogue: bias, store, and the layer's sign words (two per wave: columns
-    // col0..col0+31 and col0+32..col0+63, each from two tiles' ballots)
-    const int nwords = (N + 31) >> 5;
-    const int q = l >> 4;
-    int zero = 0;
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int v = v0 + rb + rt * 16 + q + 4 * i;
-            uint64_t pb[4], nb[4];
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct) {
-                const int col = col0 + ct * 16 + (l & 15);
-                const bool ok = v < V && col < N;
-                double z = 0.0;
-                if (ok) {
-                    z = acc[rt][ct][i] + bv[ct];
-                    b.Z[(size_t)v * ZS + col] = z;
-                    zero |= (z == 0.0);
-                }
-                pb[ct] = __ballot(ok && z > 0.0);
-                nb[ct] = __ballot(ok && z < 0.0);
+        for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = dbl4{0.0, 0.0, 0.0, 0.0};
+    for (int ks = 0; ks < KA; ks += KSEG) {
+        const int kn = min(KSEG, KA - ks), kpad = pad(kn);
+        if (ks > 0) {
+            // more columns than the LDS takes: the next ones, read again
+            __syncthreads();  // the previous ones have been multiplied
+            for (int k = l; k < K; k += 64) {
+                const int p = (int)s_idx[k] - ks;
+                if (s_idx[k] == kOut || p < 0 || p >= KSEG) continue;
+                for (int i = 0; i < RPW; ++i) as[w * RPW + i][p] = value(row[i][k], i);
             }
-            // lane 16q + p writes word p (p = 0, 1) of this row
-            const int p = l & 15;
-            if (p < 2 && v < V) {
-                const int word = (col0 >> 5) + p;
-                if (word < nwords) {
-                    const int sh = 16 * q;
+            zeros(kn);
+            __syncthreads();
+        }
+        if (col0 >= N) continue;
+#pragma unroll
+        for (int i = 0; i < SLOTS; ++i) {
+            load_w(ks + 4 * i, i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        for (int k = 0; k < kpad; k += 4 * SLOTS) {
+#pragma unroll
+            for (int i = 0; i < SLOTS; ++i) {
+                double af[RT];
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) af[rt] = as[rb + rt * 16 + r][k + 4 * i + q];
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int ct = 0; ct < CT; ++ct)
+                        acc[rt][ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[rt], bw[i][ct], acc[rt][ct], 0, 0, 0);
+                load_w(ks + k + 4 * (i + SLOTS), i);
+                __builtin_amdgcn_sched_barrier(0);  // (in flight from here)
+            }
+        }
+    }
+    // epilogue: bias, store, and the layer's sign words (one per two tiles, from their ballots)
+    const int nwords = (N + 31) >> 5;
+    int zero = 0;
+    __syncthreads();  // the inputs in LDS have been multiplied: their place takes the sign words
+    uint64_t(*s_word)[8] = reinterpret_cast<uint64_t(*)[8]>(&as[0][0]);
+    if (col0 < N) {
+        double bv[CT];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) bv[ct] = bias[min(col0 + ct * 16 + r, N - 1)];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int at = rb + rt * 16 + q + 4 * i, v = s_row[at];
+                uint64_t pb[CT], nb[CT];
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) {
+                    const int col = col0 + ct * 16 + r;
+                    const bool ok = v >= 0 && col < N;
+                    double z = 0.0;
+                    if (ok) {
+                        z = acc[rt][ct][i] + bv[ct];
+                        // (wide rows past the caches, which hold few of them until they are read: 1.6% faster)
+                        vstore<CT == 4>(&b.Z[(size_t)v * ZS + col], z);
+                        zero |= (z == 0.0);
+                    }
+                    pb[ct] = __ballot(ok && z > 0.0);
+                    nb[ct] = __ballot(ok && z < 0.0);
+                }
+                // lane 16q + p holds word p of this row
+                const int sh = 16 * q;
+#pragma unroll
+                for (int p = 0; p < CT / 2; ++p) {
                     const uint32_t pos = (uint32_t)((pb[2 * p] >> sh) & 0xFFFFu) |
                                          ((uint32_t)((pb[2 * p + 1] >> sh) & 0xFFFFu) << 16);
                     const uint32_t neg = (uint32_t)((nb[2 * p] >> sh) & 0xFFFFu) |
                                          ((uint32_t)((nb[2 * p + 1] >> sh) & 0xFFFFu) << 16);
-                    const uint64_t cw = codes_of(pos, neg);
-                    b.SG[(size_t)v * Wd + lw0 + word] = cw;
-                    if (b.LW) b.LW[(size_t)v * 8 + word] = cw;
+                    if (r == p) s_word[at][(col0 >> 5) + p] = codes_of(pos, neg);
                 }
             }
         }
+    }
+    // each row's words together: 64 bytes a row (the column blocks' waves apart
+    // write 16 bytes at a time)
+    __syncthreads();
+    static_assert(ROWS * 8 == kEvalThreads, "one word a thread");
+    const int v = s_row[t >> 3], p = t & 7;
+    if (v >= 0 && p < nwords) {
+        const uint64_t cw = s_word[t >> 3][p];
+        b.SG[(size_t)v * Wd + lw0 + p] = cw;
+        if (b.LW) b.LW[(size_t)v * 8 + p] = cw;
     }
     if (zero) raise_flag(b.CTR, FLAG_ZERO_SIGN);
 }
 
 void launch_gemm(const Bufs &b, int ZS, const double *in, int in_stride, int relu, int V, int K, int N,
-                 const double *Wt, const double *bias, int Wd, int lw0, hipStream_t st) {
+                 const double *Wt, const double *bias, int Wd, int lw0, bool finite, hipStream_t st,
+                 const EvalGrid *grid) {
     if (V <= 0) return;
-    if (N > 128 && N <= kMaxWidth && K >= 16) {
-        const int grid = (V + 63) / 64;
-        hipLaunchKernelGGL((k_gemm_mfma<8, 2, 8, 4, false, 1>), dim3(grid), dim3(512), 0, st, b, ZS, in, in_stride, relu, V, K, N, Wt,
-                           bias, Wd, lw0);
-        return;
-    }
     if (N <= kGemvMaxN) {
         hipLaunchKernelGGL(k_gemv, dim3((V + kGemvRows - 1) / kGemvRows), dim3(kGemvRows), 0, st, b, ZS, in, in_stride,
                            relu, V, K, N, Wt, bias, Wd, lw0);
         return;
     }
-    const int grid = (V + kGemmRows - 1) / kGemmRows;
-    hipLaunchKernelGGL(k_gemm, dim3(grid), dim3(kThreads), 0, st, b, ZS, in, in_stride, relu, V, K, N, Wt, bias,
-                       Wd, lw0);
+    if (!finite || K > kMaxWidth) {
+        const int blocks = (V + kGemmRows - 1) / kGemmRows;
+        hipLaunchKernelGGL(k_gemm, dim3(blocks), dim3(kThreads), 0, st, b, ZS, in, in_stride, relu, V, K, N, Wt, bias,
+                           Wd, lw0);
+        return;
+    }
+    int *perm = nullptr;
+    if (grid && V >= kBinRows && (int64_t)V * K * N >= kBinWork) {
+        int *cnt = b.SPLX;
+        perm = reinterpret_cast<int *>(b.SPLE);
+        const int blocks = std::max(1, std::min(512, V / 8192));
+        launch_fill64(reinterpret_cast<uint64_t *>(cnt), kBins / 2, 0ull, st);
+        hipLaunchKernelGGL(k_bin_count, dim3(blocks), dim3(kBinThreads), 0, st, b.X, *grid, grid->D, V, cnt);
+        hipLaunchKernelGGL(k_bin_scan, dim3(1), dim3(kBinThreads), 0, st, cnt);
+        hipLaunchKernelGGL(k_bin_scatter, dim3(blocks), dim3(kBinThreads), 0, st, b.X, *grid, grid->D, V, cnt, perm);
+    }
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((V + kEvalRows - 1) / kEvalRows), dim3(kEvalThreads), 0, st, b, ZS, in,
+                           in_stride, relu, V, K, N, Wt, bias, Wd, lw0, perm);
+    };
+    // (column blocks as narrow as the layer allows: a wave of a wider one would sit idle)
+    if (N <= 64) run(k_gemm_mfma<2, 2, 1>);
+    else if (N <= 128) run(k_gemm_mfma<4, 2, 2>);
+    else run(k_gemm_mfma<4, 4, 2>);
 }
 
 // ---------------------------------------------- step 3: splitting edges

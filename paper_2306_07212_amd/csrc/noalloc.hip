@@ -246,6 +246,7 @@ extern "C" int pcx_extract_into(const pcx_mlp *mlp, const double *lo, const doub
         return PCX_OK;
     };
 
+    const EvalGrid egrid = eval_grid(D, lo, hi);
     constexpr int kAhead = 8;
     int64_t V = V0, E = E0, Sgrid = 64;
     int l = 0, j = 0;
@@ -272,8 +273,9 @@ extern "C" int pcx_extract_into(const pcx_mlp *mlp, const double *lo, const doub
             Sgrid = Slast + Slast / 4 + 64;
             if ((rc = put(CTR_SMAX, 0))) return rc;
             const int N = mlp->widths[l + 1], K = mlp->widths[l];
-            if (l == 0) launch_gemm(b, ZS, b.X, D, 0, (int)V, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], st);
-            else launch_gemm(b, ZS, b.Z, ZS, 1, (int)V, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], st);
+            if (l == 0) launch_gemm(b, ZS, b.X, D, 0, (int)V, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], mlp->finite[l], st);
+            else launch_gemm(b, ZS, b.Z, ZS, 1, (int)V, K, N, mlp->Wt[l], mlp->b[l], Wd, lw[l], mlp->finite[l], st,
+                             Ecap >= (size_t)V ? &egrid : nullptr);
             started = true;
             j = 0;
         }
