@@ -124,10 +124,11 @@ void pcx_mlp_free(pcx_mlp *mlp);
  * steps differ from the log is discarded and the ordinary path runs. A capture
  * waits for no other call: while another thread of the process is inside a
  * device allocation or free of this library it is skipped until a later
- * request. A network whose predicted complex is small (at most 15000 vertices
- * for D <= 2, 3500 for D = 3; never for D >= 4) runs as a batch of one instead
- * (one launch of the batched kernel, the same complex; PCX_NO_TINY=1 turns
- * this off, PCX_TINY_VERTICES sets the threshold for every D). */
+ * request. A network with layers of at most 64 neurons whose predicted complex
+ * is small (at most 15000 vertices for D <= 2, 4200 for D = 3, 1800, 500 and
+ * 120 for D = 4, 5 and 6) runs as a batch of one instead (one launch, the same
+ * complex; PCX_NO_TINY=1 turns this off, PCX_TINY_VERTICES sets the threshold
+ * for every D). */
 int pcx_extract(const pcx_mlp *mlp, const double *lo, const double *hi, const pcx_opts *opts,
                 pcx_complex **out);
 
@@ -200,7 +201,9 @@ int pcx_complex_kernel_time(const pcx_complex *cx, int32_t family, double *ms, i
 void pcx_complex_free(pcx_complex *cx);
 
 /* ---- Batched extraction: many networks in one persistent launch ----------
- * Each network is extracted exactly as pcx_extract would (same vertex and edge
+ * (Under the default schedule a batch of networks with layers of at most 64
+ * neurons runs by larger workgroups, one a compute unit whatever
+ * batch_wg_per_cu.) Each network is extracted exactly as pcx_extract would (same vertex and edge
  * numbering, bit-identical values); a workgroup runs one network at a time
  * from a largest-first queue. Networks that exceed the batched kernel's limits
  * (D > 8, more than 8 layers, a layer wider than 256, or a predicted complex

@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpcx.so")
-SOURCES = ["kernels.hip", "prune.hip", "cells.hip", "backward.hip", "batch.hip", "api.hip", "batch_api.hip", "server.hip",
+SOURCES = ["kernels.hip", "prune.hip", "cells.hip", "backward.hip", "batch.hip", "small.hip", "api.hip", "batch_api.hip", "server.hip",
            "noalloc.hip", "graph.hip"]
 
 
@@ -37,7 +37,7 @@ def flags():
 # per-source additions: the batched kernel's MFMAs accumulate in ordinary
 # VGPRs (accumulation registers would add to the split's register count and
 # halve the kernel's occupancy)
-EXTRA = {"batch.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for f in ("batch.hip", "small.hip")}
 
 
 def build(verbose: bool = False) -> str:

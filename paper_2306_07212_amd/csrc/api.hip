@@ -498,13 +498,22 @@ struct Domain {
     std::vector<int2> E0;                       // [ne]
 };
 
-// Small networks go to the batched kernel as a batch of one: one launch
-// instead of several per neuron step, the same complex (PCX_NO_TINY=1 in the
-// environment turns it off). Up to which predicted vertex count, by input
-// dimension: where one workgroup stops being faster than the per-step kernels
-// (measured crossovers near 10,000 actual vertices for D = 2 and 2,800 for
-// D = 3; for D >= 4 the per-step kernels were faster at nearly every size tried).
-double tiny_vertices(int D) { return D <= 2 ? 15000.0 : D == 3 ? 3500.0 : 0.0; }
+// Small networks with layers of at most kSmallWidth neurons go to the
+// small-network kernel as a batch of one: one launch instead of two per neuron
+// step, the same complex (PCX_NO_TINY=1 in the environment turns it off). Up to
+// which predicted vertex count, by input dimension: where one workgroup stops
+// being faster than the per-step kernels, whole calls of networks extracted
+// before / replayed from a graph:
+//   D = 2:  7,682 vertices 1.91 ms against 2.62 / 1.98; 11,302: 2.75, 2.91 / 2.38
+//   D = 3:  2,717: 0.46, 0.62 / 0.48; 4,822: 0.74, 0.74 / 0.52
+//   D = 4:  1,250: 0.25, 0.40 / 0.28; 2,593: 0.44, 0.48 / 0.34
+//   D = 5:  1,047: 0.21, 0.33 / 0.22; D = 6: 789: 0.17, 0.29 / 0.18
+// (wider layers: the batched kernel's 256-thread workgroup took 2.8 ms for
+// 2-100-30-1, the per-step kernels 2.0 / 1.7).
+double tiny_vertices(int D) {
+    static const double limit[7] = {0.0, 15000.0, 15000.0, 4200.0, 1800.0, 500.0, 120.0};
+    return D <= 6 ? limit[D] : 0.0;
+}
 bool tiny_eligible(const pcx_mlp *mlp, const pcx_opts &o, int nsub) {
     const char *off = getenv("PCX_NO_TINY");
     if (off && off[0] == '1') return false;
@@ -512,7 +521,7 @@ bool tiny_eligible(const pcx_mlp *mlp, const pcx_opts &o, int nsub) {
     if (mlp->D > kBatchMaxD || mlp->L > kBatchMaxLayers) return false;
     int N = 0, Wd = 1;
     for (int l = 1; l <= nsub; ++l) {
-        if (mlp->widths[l] > kMaxWidth) return false;
+        if (mlp->widths[l] > kSmallWidth) return false;
         N += mlp->widths[l];
         Wd += (mlp->widths[l] + 31) / 32;
     }

@@ -70,5 +70,9 @@ inline size_t batch_arena_bytes(size_t vbytes, int ecap, int kcap, uint32_t tcap
 }
 
 void launch_batch(const BatchArgs &A, int grid, int sched, hipStream_t st);
+// the same for networks whose subdivided layers have at most kSmallWidth
+// neurons, by workgroups of 512 threads, one a CU
+constexpr int kSmallWidth = 64;
+void launch_small(const BatchArgs &A, int grid, hipStream_t st);
 
 }  // namespace pcx

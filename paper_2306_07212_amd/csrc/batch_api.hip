@@ -87,6 +87,14 @@ int launch_events(hipEvent_t &a, hipEvent_t &b) {
     return PCX_OK;
 }
 
+// Vertices that a batched network of this prediction gets room for. The
+// prediction is rough for small networks (up to four times too low for D >= 5),
+// and a network that does not fit is extracted a second time: more room there
+// than a quarter on top.
+size_t vertex_room(double pred) {
+    return std::max<size_t>((size_t)(pred * 1.25) + 64, std::min<size_t>((size_t)(pred * 4.0) + 512, 8192));
+}
+
 size_t align16(size_t x) { return (x + 15) / 16 * 16; }
 
 }  // namespace
@@ -127,6 +135,7 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
     size_t box_off = 0;
     int maxD = 1, maxWd = 1, maxZS = 1;
     double predV = 0;
+    bool narrow = true;  // every batched network has layers of at most kSmallWidth neurons
     for (int i = 0; i < n; ++i) {
         const pcx_mlp *m = mlps[i];
         if (!m) {
@@ -186,6 +195,7 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
             maxD = std::max(maxD, D);
             maxWd = std::max(maxWd, Wd);
             maxZS = std::max(maxZS, ZS);
+            narrow = narrow && ZS <= kSmallWidth && D <= 8;
             predV = std::max(predV, pred[i]);
         } else {
             direct.push_back(i);
@@ -211,7 +221,7 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         // per-workgroup arena from the largest batched network
         const int P = 2 * (maxD - 1) > 0 ? 2 * (maxD - 1) : 1;
-        size_t vcap = (size_t)(predV * 1.25) + 64;
+        size_t vcap = vertex_room(predV);
         size_t vbytes = vcap * 8 * (size_t)(maxD + maxWd + maxZS);
         vbytes = (vbytes + 255) / 256 * 256;
         int ecap = (int)(((size_t)vcap * (maxD + 1) + 15) / 16 * 16);
@@ -241,16 +251,19 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
         if (force_sched >= 0) sched = force_sched;
         bt->sched = sched;
         int grid = std::min<int>((int)batched.size(), cus * wpc);
+        // narrow networks under the default schedule: the small-network kernel
+        const bool small = narrow && sched == kSchedDefault;
+        if (small) grid = std::min(grid, cus);
         // output pool from the predictions (overflowing networks fall back)
         double sv = 0, ssg = 0, se = 0;
         for (int i : batched) {
-            const double v = std::min(pred[i], (double)vcap);
+            const double v = std::min((double)vertex_room(pred[i]), (double)vcap);
             sv += v * bt->D[i];
             ssg += v * bt->Wd[i];
             se += v * (bt->D[i] + 1);
         }
-        const unsigned long long capV = (unsigned long long)(sv * 1.1) + 1024, capSG = (unsigned long long)(ssg * 1.1) + 1024,
-                                 capE = (unsigned long long)(se * 1.1) + 1024;
+        const unsigned long long capV = (unsigned long long)sv + 1024, capSG = (unsigned long long)ssg + 1024,
+                                 capE = (unsigned long long)se + 1024;
         void *p;
         BatchArgs A{};
         if ((rc = ar.alloc(&p, (size_t)grid * abytes))) goto fail_out;
@@ -338,7 +351,8 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
             hipEvent_t e0, e1;
             if ((rc = launch_events(e0, e1))) goto fail_out;
             HIPCHK(hipEventRecord(e0, st));
-            launch_batch(A, grid, sched, st);
+            if (small) launch_small(A, grid, st);
+            else launch_batch(A, grid, sched, st);
             HIPCHK(hipGetLastError());
             HIPCHK(hipEventRecord(e1, st));
             // (stream order: the input copy out of the staging buffer is done before this one lands there)

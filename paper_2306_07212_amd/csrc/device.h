@@ -198,13 +198,48 @@ __device__ __forceinline__ int slot_partner(const Bufs &b, const StepGeom &g, in
     return (int)(p1 - 1u);
 }
 
+// Where a step keeps its key slots, its 2-face table and the edges' next
+// crossings: the arrays of Bufs and StepGeom. (The small-network kernel has the
+// same in LDS.)
+struct GlobalMem {
+    __device__ __forceinline__ void next(const Bufs &b, const StepGeom &g, size_t e, int col) const {
+        if (g.nx8)  // crossings after the neuron: 1..255
+            b.NX8[e] = col == kNoCol ? 0 : (uint8_t)col;
+        else
+            b.NXT[e] = col == kNoCol ? kNone : (uint16_t)col;
+    }
+    __device__ __forceinline__ uint32_t info(const Bufs &b, size_t slot) const { return b.PINFO[slot]; }
+    // key slot `slot` perturbs entry `info` and has the 2-face hash H
+    __device__ __forceinline__ void key(const Bufs &b, const StepGeom &g, size_t slot, uint32_t info, uint64_t H,
+                                        int nslots) const {
+        b.PINFO[slot] = info;
+        if (g.pair_mode == PAIR_SORT) {
+            // 24 bits for three 8-bit radix passes; all-ones is the sentinel's
+            const uint32_t k24 = (uint32_t)(H >> 40);
+            b.K32a[slot] = k24 < 0xFFFFFFu ? k24 : 0xFFFFFEu;
+            b.FULL[slot] = H;
+        } else if (g.hmask != 0u) {  // (0: more key slots than the table names; the exact pass pairs the step)
+            hash_insert(b, g, H, (uint32_t)slot, nslots);
+        }
+    }
+    __device__ __forceinline__ void unused(const Bufs &b, const StepGeom &g, size_t slot) const {
+        b.PINFO[slot] = kNoInfo;
+        if (g.pair_mode == PAIR_SORT) b.K32a[slot] = kSentinel;
+    }
+    __device__ __forceinline__ int partner(const Bufs &b, const StepGeom &g, int u, int nslots) const {
+        return slot_partner(b, g, u, nslots);
+    }
+};
+
 // Key slot u at the pairing's check: true if u owns a pair (the smaller slot
 // of a mutual pair of fresh records). A valid slot without a fresh mutual
 // record is a pairing failure of the step.
-__device__ __forceinline__ bool slot_owner(const Bufs &b, const StepGeom &g, int u, int nslots, int &partner) {
-    if (b.PINFO[u] == kNoInfo) return false;
-    const int p = slot_partner(b, g, u, nslots);
-    if (p < 0 || slot_partner(b, g, p, nslots) != u) {
+template <class M = GlobalMem>
+__device__ __forceinline__ bool slot_owner(const Bufs &b, const StepGeom &g, int u, int nslots, int &partner,
+                                           const M &m = M()) {
+    if (m.info(b, u) == kNoInfo) return false;
+    const int p = m.partner(b, g, u, nslots);
+    if (p < 0 || m.partner(b, g, p, nslots) != u) {
         raise_pair_flag(b.CTR, FLAG_RUN, g.step);
         return false;
     }
@@ -218,9 +253,10 @@ __device__ __forceinline__ bool slot_owner(const Bufs &b, const StepGeom &g, int
 // stored 64-bit hashes (the hash table already matched them exactly). preA:
 // words wn .. wn+3 of sa's row, when the caller has loaded them already.
 // Returns the edge's first crossing in the layer (kNoCol: none).
+template <class M = GlobalMem>
 __device__ __forceinline__ int emit_pair(const Bufs &b, const StepGeom &g, int V0, int nslots, int sa, int sb,
                                           size_t out, bool check_hash = true, bool check_rows = true,
-                                          const uint64_t *preA = nullptr) {
+                                          const uint64_t *preA = nullptr, const M &m = M()) {
     if ((unsigned)sa >= (unsigned)nslots || (unsigned)sb >= (unsigned)nslots) {
         raise_flag(b.CTR, FLAG_BOUNDS);
         return kNoCol;
@@ -229,7 +265,7 @@ __device__ __forceinline__ int emit_pair(const Bufs &b, const StepGeom &g, int V
     const uint64_t *Ra = b.SG + (size_t)xa * g.Wd, *Rb = b.SG + (size_t)xb * g.Wd;
     uint64_t diff = check_hash ? (b.FULL[sa] ^ b.FULL[sb]) : 0ull;
     if (check_rows) {
-        const uint32_t pa = b.PINFO[sa], pb = b.PINFO[sb];
+        const uint32_t pa = m.info(b, sa), pb = m.info(b, sb);
         const int wa = (int)(pa >> 8), wb = (int)(pb >> 8);
         const uint64_t ca = ((pa & 1u) ? 2ull : 1ull) << ((pa >> 1) & 63u);
         const uint64_t cb = ((pb & 1u) ? 2ull : 1ull) << ((pb >> 1) & 63u);
@@ -258,10 +294,7 @@ __device__ __forceinline__ int emit_pair(const Bufs &b, const StepGeom &g, int V
             if (x[i]) col = first_col(x[i], w0 + i, g.lw0);
     }
     b.EDG[out] = make_int2(xa, xb);
-    if (g.nx8)
-        b.NX8[out] = col == kNoCol ? 0 : (uint8_t)col;  // col > j >= 0
-    else
-        b.NXT[out] = col == kNoCol ? kNone : (uint16_t)col;
+    m.next(b, g, out, col);
     return col;
 }
 
@@ -360,10 +393,11 @@ __device__ __forceinline__ void vstore(T *p, T v) {
     else *p = v;
 }
 
-// split_core: the split of edge e = ab (already read and bounds-checked)
-template <int G, int NC, bool NT>
+// split_core: the split of edge e = ab (already read and bounds-checked), by a
+// group of a workgroup of T threads
+template <int G, int NC, bool NT, int T = kThreads, class M = GlobalMem>
 __device__ __forceinline__ void split_core(const Bufs &b, const StepGeom &g, int V0, int E0, int s, int e, int2 ab,
-                                           int lane, int half, int nslots) {
+                                           int lane, int half, int nslots, const M &m = M()) {
     const int D = g.D, Wd = g.Wd, ZS = g.ZS;
     // every 2-face key of the split is built by a lane of the group (callers
     // choose G >= 2(D - 1)); anything else is refused as an internal error
@@ -407,8 +441,7 @@ __device__ __forceinline__ void split_core(const Bufs &b, const StepGeom &g, int
     // add no bit to either ballot. Column j is interpolated like the others:
     // every use of its ballot bits below is masked to the entries after j, and
     // its stored value is overwritten by an exact 0.
-    __shared__ uint64_t s_bal[kThreads / 64][kMaxWidth / 32][2];
-    static_assert(G == 64 ? NC <= kMaxWidth / 64 : NC <= kMaxWidth / 32, "chunk ballots exceed the LDS slots");
+    __shared__ uint64_t s_bal[T / 64][NC][2];
     static_assert(G != 16 || NC % 2 == 0, "16-lane groups take whole 32-column words");
     const int wv = threadIdx.x >> 6;
 #pragma unroll
@@ -528,13 +561,8 @@ __device__ __forceinline__ void split_core(const Bufs &b, const StepGeom &g, int
         if (bad) raise_flag(b.CTR, bad);
         b.EDG[e] = make_int2(ab.x, (int)x0);
         b.EDG[E0 + s] = make_int2((int)x0, ab.y);
-        if (g.nx8) {  // crossings after j >= 0: 1..255
-            b.NX8[e] = da == kNoCol ? 0 : (uint8_t)da;
-            b.NX8[E0 + s] = db == kNoCol ? 0 : (uint8_t)db;
-        } else {
-            b.NXT[e] = da == kNoCol ? kNone : (uint16_t)da;
-            b.NXT[E0 + s] = db == kNoCol ? kNone : (uint16_t)db;
-        }
+        m.next(b, g, e, da);
+        m.next(b, g, (size_t)E0 + s, db);
         if (b.PQ) b.PQ[x0] = apos ? ab : make_int2(ab.y, ab.x);
     }
     if (g.P > 0) {
@@ -548,20 +576,9 @@ __device__ __forceinline__ void split_core(const Bufs &b, const StepGeom &g, int
             // (hkeep drops hash bits only to test the exact pass: collisions on purpose)
             const uint64_t myh = (hsum - word_hash(kw, kf) + word_hash(kw, kf | ((minus ? 2ull : 1ull) << bit))) & g.hkeep;
             const size_t slot = sbase + lane;
-            b.PINFO[slot] = ((uint32_t)kw << 8) | ((uint32_t)bit << 1) | (uint32_t)minus;
-            if (g.pair_mode == PAIR_SORT) {
-                // 24 bits for three 8-bit radix passes; all-ones is the sentinel's
-                const uint32_t k24 = (uint32_t)(myh >> 40);
-                b.K32a[slot] = k24 < 0xFFFFFFu ? k24 : 0xFFFFFEu;
-                b.FULL[slot] = myh;
-            } else if (g.hmask != 0u) {  // (0: more key slots than the table names; the exact pass pairs the step)
-                hash_insert(b, g, myh, (uint32_t)slot, nslots);
-            }
+            m.key(b, g, slot, ((uint32_t)kw << 8) | ((uint32_t)bit << 1) | (uint32_t)minus, myh, nslots);
         }
-        for (int rr = ktot + lane; rr < g.P; rr += G) {
-            b.PINFO[sbase + rr] = kNoInfo;
-            if (g.pair_mode == PAIR_SORT) b.K32a[sbase + rr] = kSentinel;
-        }
+        for (int rr = ktot + lane; rr < g.P; rr += G) m.unused(b, g, sbase + rr);
     }
 }
 
