@@ -243,7 +243,9 @@ struct Extraction {
         if (tape) {
             size_t c3 = Vcap;
             if ((rc = grow_keep(b.PQ, c3, need, used, 1))) return rc;
-            c2 = std::min(c2, c3);
+            size_t c4 = Vcap;
+            if ((rc = grow_keep(b.DEP, c4, need, used, 1))) return rc;
+            c2 = std::min({c2, c3, c4});
         }
         Vcap = std::min(c0, std::min(c1, c2));
         return PCX_OK;
@@ -674,6 +676,8 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
         HIPCHK(hipMemcpyAsync(x.b.EDG, dom.E0.data(), E0 * sizeof(int2), hipMemcpyHostToDevice, st));
         HIPCHK(hipStreamSynchronize(st));  // the host vectors are not kept
     }
+    // (the domain's vertices belong to no layer)
+    if (x.tape) launch_fill64(reinterpret_cast<uint64_t *>(x.b.DEP), (V0 + 1) / 2, 0ull, st);
     HIPCHK(hipGetLastError());
 
     std::vector<int64_t> steps((size_t)n_steps * 4, 0);
@@ -1000,6 +1004,7 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
             if ((rc = x.mark(PCX_K_PAIR, false))) return rc;
             HIPCHK(hipGetLastError());
         } else if (S * x.P > 0) {
+            if (x.tape) launch_tape_depths(x.b, g, (int)S, st);
             if ((rc = x.mark(PCX_K_SORT, true))) return rc;
             const uint32_t *skeys = nullptr, *svals = nullptr;
             launch_sort(x.b, (int)(S * x.P), st, &skeys, &svals);
@@ -1010,6 +1015,7 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
             if ((rc = x.mark(PCX_K_PAIR, false))) return rc;
             HIPCHK(hipGetLastError());
         } else {
+            if (x.tape) launch_tape_depths(x.b, g, (int)S, st);
             if ((rc = x.put_ctr(CTR_E + (par ^ 1), (int)(E + S)))) return rc;
         }
         ++j;
@@ -1067,8 +1073,10 @@ int extract_impl(const pcx_mlp *mlp, const Domain &dom, const pcx_opts *opts, pc
         tapeZ.push_back(x.b.Z);
         for (double *z : tapeZ) x.arena.forget(z);
         x.arena.forget(x.b.PQ);
+        x.arena.forget(x.b.DEP);
         cx->taped = true;
         cx->PQ = x.b.PQ;
+        cx->DEP = x.b.DEP;
         cx->Zl = tapeZ;
         int s0 = 0;
         for (int l = 0; l < nsub; ++l) {
@@ -1227,6 +1235,7 @@ void pcx_complex_free(pcx_complex *cx) {
     pool().put(cx->SG);
     pool().put(cx->EDG);
     pool().put(cx->PQ);
+    pool().put(cx->DEP);
     for (double *z : cx->Zl) pool().put(z);
     delete cx;
 }
@@ -1267,10 +1276,18 @@ int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad,
     const int Vb = cx->n_steps > 0 ? (int)cx->steps[0] : (int)cx->V;
     const int nrec = 2 * (int)(cx->V - Vb);
     Bufs sb{};
-    int *pos = nullptr;
+    int2 *range = nullptr;
+    int *order = nullptr, *depths = nullptr;
     double *tt = nullptr;
-    T *gtt = nullptr;
+    T *gp = nullptr, *gq = nullptr;
     const uint64_t *skey = nullptr;
+    constexpr int kDepths = kMaxDepth + 1;
+    std::vector<int> lw(nsub + 1, 1), Vstart(nsub + 1, (int)cx->V);
+    for (int l = 0; l < nsub; ++l) {
+        lw[l + 1] = lw[l] + (mlp->widths[l + 1] + 31) / 32;
+        Vstart[l] = (int)cx->steps[(size_t)cx->layer_step0[l] * 4];
+    }
+    std::vector<int> count((size_t)nsub * kDepths, 0), place((size_t)nsub * kDepths, 0);
     if (nrec > 0) {
         if ((rc = ar.alloc(&p, (size_t)nrec * sizeof(uint64_t)))) return rc;
         sb.K64a = (uint64_t *)p;
@@ -1283,16 +1300,43 @@ int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad,
         if ((rc = ar.alloc(&p, (size_t)kSortBins * ((nrec + kSortTile - 1) / kSortTile + 1) * sizeof(uint32_t))))
             return rc;
         sb.HIST = (uint32_t *)p;
-        if ((rc = ar.alloc(&p, (size_t)nrec * sizeof(int)))) return rc;
-        pos = (int *)p;
+        if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(int2)))) return rc;
+        range = (int2 *)p;
+        if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(int)))) return rc;
+        order = (int *)p;
+        if ((rc = ar.alloc(&p, (size_t)nsub * kDepths * sizeof(int)))) return rc;
+        depths = (int *)p;
         if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(double)))) return rc;
         tt = (double *)p;
         if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(T)))) return rc;
-        gtt = (T *)p;
+        gp = (T *)p;
+        if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(T)))) return rc;
+        gq = (T *)p;
+        // each layer's new vertices by depth
+        HIPCHK(hipMemsetAsync(depths, 0, (size_t)nsub * kDepths * sizeof(int), st));
+        for (int l = 0; l < nsub; ++l)
+            bwd_depth_count(cx->DEP, lw[l], Vstart[l], Vstart[l + 1], depths + l * kDepths, dflag, st);
+        HIPCHK(hipMemcpyAsync(count.data(), depths, count.size() * sizeof(int), hipMemcpyDeviceToHost, st));
+        // (the records come in child order and the sort is stable: only the parents' bits are sorted)
+        int bytes = 1;
+        while (bytes < 4 && (cx->V >> (8 * bytes)) != 0) ++bytes;
         bwd_records(cx->PQ, Vb, (int)cx->V, sb.K64a, dflag, st);
         const uint32_t *svals = nullptr;
-        launch_sort64(sb, nrec, st, &skey, &svals);
-        bwd_pos(svals, nrec, pos, st);
+        launch_sort64(sb, nrec, st, &skey, &svals, 4, bytes);
+        bwd_ranges(skey, nrec, (int)cx->V, range, st);
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipStreamSynchronize(st));
+        for (int l = 0; l < nsub; ++l) {
+            int at = Vstart[l] - Vb;
+            for (int d = 1; d < kDepths; ++d) {
+                place[(size_t)l * kDepths + d] = at;
+                at += count[(size_t)l * kDepths + d];
+            }
+            if (at != Vstart[l + 1] - Vb) return fail(PCX_ERR_DEVICE, "internal error: tape depth out of range");
+        }
+        HIPCHK(hipMemcpyAsync(depths, place.data(), place.size() * sizeof(int), hipMemcpyHostToDevice, st));
+        for (int l = 0; l < nsub; ++l)
+            bwd_depth_order(cx->DEP, lw[l], Vstart[l], Vstart[l + 1], depths + l * kDepths, order, st);
         HIPCHK(hipGetLastError());
     }
     // layers that were not subdivided do not move any vertex
@@ -1302,15 +1346,16 @@ int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad,
     }
     for (int l = nsub - 1; l >= 0; --l) {
         const int N = mlp->widths[l + 1], K = mlp->widths[l];
-        const int s0 = cx->layer_step0[l];
-        for (int j = N - 1; j >= 0; --j) {
-            const int64_t *st4 = &cx->steps[(size_t)(s0 + j) * 4];
-            bwd_step<T>(cx->X, cx->Zl[l], cx->PQ, gx, gz, D, N, ZS, j, Vb, (int)st4[0], (int)st4[2], skey, nrec, pos,
-                        tt, gtt, dflag, st);
+        const int Vs = Vstart[l];
+        if (Vstart[l + 1] > Vs) {
+            BwdLayer<T> L{cx->X, cx->Zl[l], cx->PQ, cx->DEP, skey, range, Vs, Vstart[l + 1], D, N, ZS,
+                          gx, gz, tt, gp, gq};
+            for (int d = kDepths - 1; d >= 1; --d)
+                bwd_pull<T>(L, order + place[(size_t)l * kDepths + d], count[(size_t)l * kDepths + d], st);
+            bwd_pull<T>(L, nullptr, Vs, st);  // depth 0: the vertices from before the layer
+            HIPCHK(hipGetLastError());
         }
-        HIPCHK(hipGetLastError());
-        const int Vs = (int)cx->steps[(size_t)s0 * 4];
-        const int chunks = std::max(1, std::min(256, Vs / 2048));
+        const int chunks = bwd_chunks(Vs, N, K);
         if ((rc = ar.alloc(&p, (size_t)chunks * N * (K + 1) * sizeof(double)))) return rc;
         double *part = (double *)p;
         T *gzp = nullptr;
@@ -1322,11 +1367,8 @@ int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad,
         bwd_layer<T>(gz, ZS, hin, l == 0 ? D : ZS, l > 0 ? 1 : 0, Vs, N, K, mlp->Wr[l], part, chunks, gW[l], gb[l],
                      gzp, ZS, st);
         HIPCHK(hipGetLastError());
-        if (gzp) {
-            HIPCHK(hipStreamSynchronize(st));
-            ar.release(gz);
-            gz = gzp;
-        }
+        // (the rows of the layers above stay allocated until the stream is done with them)
+        if (gzp) gz = gzp;
     }
     int hflag = 0;
     HIPCHK(hipMemcpyAsync(&hflag, dflag, sizeof(int), hipMemcpyDeviceToHost, st));

@@ -8,12 +8,17 @@
 // and each new vertex x0 of step (l, j) from its splitting edge (p, q), p = V+:
 //   t = z_p / (z_p - z_q),  x0 = x_p + t (x_q - x_p),
 //   Z(x0)[c] = Z_p[c] + t (Z_q[c] - Z_p[c])  (c != j),   Z(x0)[j] = 0.
-// Reverse mode walks it back: steps in reverse order (children before their
-// parents), then each layer start. Within one step the new vertices are
-// independent; each parent then sums the contributions of its children of the
-// step itself, in increasing child order (no atomics: the gradients are the
-// same bits on every run). Every parent's children come from one sort of
-// (parent, child) records per backward call. T is the arithmetic type of the
+// Reverse mode walks it back, a layer at a time: children before their parents,
+// then the layer start. Within a layer the tape gives every new vertex its depth
+// (longest chain of parents made in the layer), and the vertices of one depth
+// are independent: one launch a depth, the deepest first, in which each vertex
+// sums the contributions of its children itself, youngest child first (no
+// atomics: the gradients are the same bits on every run). A layer of 64 neurons
+// has some 20 depths, so that is 20 launches and not two for each of 64 steps:
+// launches bound the pass (3-64-64-64-1: 2.8 ms in 364 launches of the steps,
+// now 1.3 in 54). Every
+// parent's children come from one sort of (parent, child) records per backward
+// call. T is the arithmetic type of the
 // gradients (double, or float for the throughput mode); the recorded values
 // are FP64.
 #include <hip/hip_runtime.h>
@@ -49,85 +54,147 @@ __global__ __launch_bounds__(kThreads) void k_bwd_records(const int2 *__restrict
     }
 }
 
-// position of every record in the sorted order
-__global__ __launch_bounds__(kThreads) void k_bwd_pos(const uint32_t *__restrict__ vals, int n, int *__restrict__ pos) {
-    for (int i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads) pos[vals[i]] = i;
-}
-
-// One wave per new vertex of the step: t of its splitting edge and dL/dt,
-// from its coordinates and every carried pre-activation but the current one
-// (lanes over columns, a fixed reduction order).
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_bwd_child(const double *__restrict__ X, const double *__restrict__ Zs,
-                                                         const int2 *__restrict__ PQ, const T *__restrict__ gx,
-                                                         const T *__restrict__ gz, int D, int N, int ZS, int j, int V0,
-                                                         int S, double *__restrict__ tt, T *__restrict__ gtt) {
-    const int lane = threadIdx.x & 63;
-    const int wv = (blockIdx.x * kThreads + threadIdx.x) >> 6;
-    const int nwv = gridDim.x * (kThreads / 64);
-    for (int s = wv; s < S; s += nwv) {
-        const int x0 = V0 + s;
-        const int2 pq = PQ[x0];
-        const size_t p = pq.x, q = pq.y;
-        const double zp = Zs[p * ZS + j], zq = Zs[q * ZS + j];
-        const double t = zp / (zp - zq);
-        T gt = 0;
-        for (int d = lane; d < D; d += 64) gt += gx[(size_t)x0 * D + d] * (T)(X[q * D + d] - X[p * D + d]);
-        for (int c = lane; c < N; c += 64) {
-            if (c == j) continue;
-            gt += gz[(size_t)x0 * ZS + c] * (T)(Zs[q * ZS + c] - Zs[p * ZS + c]);
-        }
-        for (int o = 32; o > 0; o >>= 1) gt += __shfl_xor(gt, o, 64);
-        if (lane == 0) {
-            tt[x0] = t;
-            gtt[x0] = gt;
-        }
+// range of every parent's records in the sorted order (the others keep (0, 0))
+__global__ __launch_bounds__(kThreads) void k_bwd_ranges(const uint64_t *__restrict__ skey, int nrec, int V,
+                                                         int2 *__restrict__ range) {
+    for (int i = blockIdx.x * kThreads + threadIdx.x; i < nrec; i += gridDim.x * kThreads) {
+        const uint32_t P = (uint32_t)(skey[i] >> 32);
+        if (P >= (uint32_t)V) continue;
+        if (i == 0 || (uint32_t)(skey[i - 1] >> 32) != P) range[P].x = i;
+        if (i == nrec - 1 || (uint32_t)(skey[i + 1] >> 32) != P) range[P].y = i + 1;
     }
 }
 
-// One wave per (new vertex, side) record of the step. The record that comes
-// first among its parent's children of this step sums, in child order, every
-// such child's contribution to the parent:
-//   dL/dx_p += (1 - t) dL/dx0,  dL/dZ_p[c] += (1 - t) dL/dZ0[c]  (c != j),
-//   dL/dz_p += dL/dt * dt/dz_p  with dt/dz_p = -z_q / (z_p - z_q)^2
-// (and with t, dt/dz_q = z_p / (z_p - z_q)^2 for the V- parent q).
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_bwd_parent(const double *__restrict__ Zs, const int2 *__restrict__ PQ,
-                                                          T *__restrict__ gx, T *__restrict__ gz, int D, int N, int ZS,
-                                                          int j, int Vb, int V0, int S,
-                                                          const uint64_t *__restrict__ skey, int nrec,
-                                                          const int *__restrict__ pos, const double *__restrict__ tt,
-                                                          const T *__restrict__ gtt, int *flag) {
-    const int lane = threadIdx.x & 63;
-    const int wv = (blockIdx.x * kThreads + threadIdx.x) >> 6;
-    const int nwv = gridDim.x * (kThreads / 64);
-    for (int r = wv; r < 2 * S; r += nwv) {
-        const int rec = 2 * (V0 - Vb) + r;
-        const int i = pos[rec];
-        if ((unsigned)i >= (unsigned)nrec) {
-            if (lane == 0) atomicOr(flag, 1);
-            continue;
+// Depths of a layer's new vertices: counts, and the vertices grouped by depth
+// (their order inside a depth does not matter).
+__global__ __launch_bounds__(kThreads) void k_bwd_depth_count(const uint32_t *__restrict__ DEP, int lw0, int Vs, int Ve,
+                                                              int *__restrict__ count, int *flag) {
+    __shared__ int h[kMaxDepth + 1];
+    for (int i = threadIdx.x; i <= kMaxDepth; i += kThreads) h[i] = 0;
+    __syncthreads();
+    for (int v = Vs + blockIdx.x * kThreads + threadIdx.x; v < Ve; v += gridDim.x * kThreads) {
+        const int d = dep_depth(DEP[v], lw0);
+        if (d < 1 || d > kMaxDepth) atomicOr(flag, 1);
+        else atomicAdd(&h[d], 1);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i <= kMaxDepth; i += kThreads)
+        if (h[i]) atomicAdd(&count[i], h[i]);
+}
+
+__global__ __launch_bounds__(kThreads) void k_bwd_depth_order(const uint32_t *__restrict__ DEP, int lw0, int Vs, int Ve,
+                                                              int *__restrict__ next, int *__restrict__ order) {
+    __shared__ int h[kMaxDepth + 1];
+    const int per = (Ve - Vs + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int v0 = min(Ve, Vs + (int)blockIdx.x * per), v1 = min(Ve, v0 + per);
+    for (int i = threadIdx.x; i <= kMaxDepth; i += kThreads) h[i] = 0;
+    __syncthreads();
+    for (int v = v0 + threadIdx.x; v < v1; v += kThreads) {
+        const int d = dep_depth(DEP[v], lw0);
+        if (d >= 1 && d <= kMaxDepth) atomicAdd(&h[d], 1);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i <= kMaxDepth; i += kThreads)
+        if (h[i]) h[i] = atomicAdd(&next[i], h[i]);  // this workgroup's places of the depth
+    __syncthreads();
+    for (int v = v0 + threadIdx.x; v < v1; v += kThreads) {
+        const int d = dep_depth(DEP[v], lw0);
+        if (d >= 1 && d <= kMaxDepth) order[atomicAdd(&h[d], 1)] = v;
+    }
+}
+
+// One group of G lanes per vertex v of one depth (lane c of chunk k holds column
+// k G + c). First what its children of the layer add, youngest first:
+//   dL/dx_v += s dL/dx0,  dL/dZ_v[c] += s dL/dZ0[c]  (c != j),
+// s = 1 - t for the V+ parent and t for the V- parent, and to dL/dz_v of the
+// child's neuron j its share of dL/dt (gp or gq). Its gradients are then
+// complete (its children's were: they are deeper), so a new vertex gets t of its
+// splitting edge, dL/dt from its coordinates and every carried pre-activation
+// but its own neuron's, and the shares
+//   gp = dL/dt * -z_q / (z_p - z_q)^2,  gq = dL/dt * z_p / (z_p - z_q)^2.
+// Bound: the latency of the chain record -> child's row, so kAhead children's
+// loads are in flight at once.
+template <typename T, int G, int NC>
+__global__ __launch_bounds__(kThreads) void k_bwd_pull(BwdLayer<T> L, const int *__restrict__ order, int n) {
+    constexpr int kAhead = 4;
+    const int lane = threadIdx.x % G;
+    const int groups = gridDim.x * (kThreads / G);
+    for (int i = (blockIdx.x * kThreads + threadIdx.x) / G; i < n; i += groups) {
+        const int v = order ? order[i] : i;
+        const int2 own = L.range[v];
+        T ax = 0, az[NC];
+        bool any = false;
+        T *gzv = L.gz + (size_t)v * L.ZS, *gxv = L.gx + (size_t)v * L.D;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const int c = k * G + lane;
+            az[k] = c < L.N ? gzv[c] : (T)0;
         }
-        const uint64_t k = skey[i];
-        const uint32_t P = (uint32_t)(k >> 32);
-        // a child of P in this step comes before: it is that one's work
-        if (i > 0 && (uint32_t)(skey[i - 1] >> 32) == P && (int)((uint32_t)skey[i - 1] >> 1) >= V0) continue;
-        for (int e = i; e < nrec; ++e) {
-            const uint64_t ke = skey[e];
-            const int c = (int)((uint32_t)ke >> 1);
-            if ((uint32_t)(ke >> 32) != P || c >= V0 + S) break;
-            const int side = (int)(ke & 1u);
-            const int2 pq = PQ[c];
-            const double zp = Zs[(size_t)pq.x * ZS + j], zq = Zs[(size_t)pq.y * ZS + j];
-            const double t = tt[c], den = zp - zq;
-            const double inv = 1.0 / (den * den);
-            const T coef = side ? (T)t : (T)(1.0 - t);
-            for (int d = lane; d < D; d += 64) gx[(size_t)P * D + d] += coef * gx[(size_t)c * D + d];
-            for (int col = lane; col < N; col += 64) {
-                if (col == j) continue;
-                gz[(size_t)P * ZS + col] += coef * gz[(size_t)c * ZS + col];
+        if (lane < L.D) ax = gxv[lane];
+        // (youngest first: later layers' children, which have been summed, are passed
+        // over, and an earlier layer's ends the list)
+        bool more = true;
+        for (int r = own.y - 1; r >= own.x && more; r -= kAhead) {
+            int child[kAhead], jn[kAhead];
+            T s[kAhead], gs[kAhead], cx[kAhead], cz[kAhead][NC];
+            bool live[kAhead];
+#pragma unroll
+            for (int a = 0; a < kAhead; ++a) {
+                const uint64_t key = L.skey[max(r - a, own.x)];
+                child[a] = (int)((uint32_t)key >> 1);
+                live[a] = r - a >= own.x && child[a] >= L.Vs && child[a] < L.Ve;
+                more = more && child[a] >= L.Vs;
+                if (!live[a]) child[a] = v;  // (a row that is there; not used)
+                const bool side = key & 1u;
+                const double t = L.tt[child[a]];
+                s[a] = side ? (T)t : (T)(1.0 - t);
+                gs[a] = side ? L.gq[child[a]] : L.gp[child[a]];
+                jn[a] = dep_neuron(L.DEP[child[a]]);
             }
-            if (lane == 0) gz[(size_t)P * ZS + j] += gtt[c] * (T)(side ? zp * inv : -zq * inv);
+#pragma unroll
+            for (int a = 0; a < kAhead; ++a) {
+                const T *gzc = L.gz + (size_t)child[a] * L.ZS;
+#pragma unroll
+                for (int k = 0; k < NC; ++k) cz[a][k] = gzc[min(k * G + lane, L.N - 1)];
+                cx[a] = L.gx[(size_t)child[a] * L.D + min(lane, L.D - 1)];
+            }
+#pragma unroll
+            for (int a = 0; a < kAhead; ++a) {
+                if (!live[a]) continue;
+                any = true;
+                ax += s[a] * cx[a];
+#pragma unroll
+                for (int k = 0; k < NC; ++k) {
+                    const int c = k * G + lane;
+                    az[k] += c == jn[a] ? gs[a] : s[a] * cz[a][k];
+                }
+            }
+        }
+        if (any) {
+#pragma unroll
+            for (int k = 0; k < NC; ++k)
+                if (k * G + lane < L.N) gzv[k * G + lane] = az[k];
+            if (lane < L.D) gxv[lane] = ax;
+        }
+        if (v < L.Vs) continue;
+        const int j = dep_neuron(L.DEP[v]);
+        const int2 pq = L.PQ[v];
+        const size_t p = pq.x, q = pq.y;
+        const double zp = L.Z[p * L.ZS + j], zq = L.Z[q * L.ZS + j], den = zp - zq;
+        T gt = 0;
+        if (lane < L.D) gt = ax * (T)(L.X[q * L.D + lane] - L.X[p * L.D + lane]);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const int c = k * G + lane;
+            if (c < L.N && c != j) gt += az[k] * (T)(L.Z[q * L.ZS + c] - L.Z[p * L.ZS + c]);
+        }
+#pragma unroll
+        for (int o = G / 2; o > 0; o >>= 1) gt += __shfl_xor(gt, o, G);
+        if (lane == 0) {
+            const double inv = 1.0 / (den * den);
+            L.tt[v] = zp / den;
+            L.gp[v] = gt * (T)(-zq * inv);
+            L.gq[v] = gt * (T)(zp * inv);
         }
     }
 }
@@ -135,7 +202,7 @@ __global__ __launch_bounds__(kThreads) void k_bwd_parent(const double *__restric
 // Partial sums of the weight and bias gradients over one chunk of vertices:
 // part[chunk][c][k] = sum_v gz[v][c] h[v][k], h = ReLU of the previous layer's
 // pre-activations (the coordinates for layer 1), and k == K is the bias
-// (h = 1). A workgroup takes a 64 x 64 tile of the (c, k) entries and its
+// (h = 1; summed by the tiles of k = 0). A workgroup takes a 64 x 64 tile of the (c, k) entries and its
 // chunk, stages 32 vertices' gz and h values of the tile through LDS at a time,
 // and each thread accumulates 4 x 4 entries. Every entry sums its chunk's
 // vertices in order, one fused multiply-add each, and k_bwd_wreduce adds the
@@ -151,11 +218,13 @@ __global__ __launch_bounds__(256) void k_bwd_wgrad_tiled(const T *__restrict__ g
     const int c0 = (blockIdx.x / tiles_k) * kWgTile, k0 = (blockIdx.x % tiles_k) * kWgTile;
     const int chunk = (Vs + gridDim.y - 1) / gridDim.y;
     const int v0 = blockIdx.y * chunk, v1 = min(Vs, v0 + chunk);
-    T acc[4][4];
+    T acc[4][4], accb[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i) {
+        accb[i] = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[i][j] = 0;
+    }
     for (int vb = v0; vb < v1; vb += kWgRows) {
         const int nv = min(kWgRows, v1 - vb);
         for (int idx = t; idx < kWgRows * kWgTile; idx += 256) {
@@ -168,8 +237,6 @@ __global__ __launch_bounds__(256) void k_bwd_wgrad_tiled(const T *__restrict__ g
                     double x = hin[(size_t)v * hstride + k];
                     if (relu) x = x > 0.0 ? x : 0.0;
                     h = (T)x;
-                } else if (k == K) {
-                    h = 1;
                 }
             }
             gs[r][q] = g;
@@ -186,6 +253,10 @@ __global__ __launch_bounds__(256) void k_bwd_wgrad_tiled(const T *__restrict__ g
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fma(a[i], bb[j], acc[i][j]);
+            if (k0 == 0 && tk == 0) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) accb[i] += a[i];
+            }
         }
         __syncthreads();
     }
@@ -193,20 +264,32 @@ __global__ __launch_bounds__(256) void k_bwd_wgrad_tiled(const T *__restrict__ g
     for (int i = 0; i < 4; ++i) {
         const int c = c0 + tc + 16 * i;
         if (c >= N) continue;
+        if (k0 == 0 && tk == 0) part[(size_t)blockIdx.y * N * (K + 1) + (size_t)c * (K + 1) + K] = (double)accb[i];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int k = k0 + tk + 16 * j;
-            if (k <= K) part[(size_t)blockIdx.y * N * (K + 1) + (size_t)c * (K + 1) + k] = (double)acc[i][j];
+            if (k < K) part[(size_t)blockIdx.y * N * (K + 1) + (size_t)c * (K + 1) + k] = (double)acc[i][j];
         }
     }
 }
 
+// the chunks' sums, 32 entries a workgroup: thread (i, y) adds the chunks y, y + 8,
+// ... of entry i in order, and the eight sums are added in order
 __global__ __launch_bounds__(kThreads) void k_bwd_wreduce(const double *__restrict__ part, int chunks, int N, int K,
                                                            double *__restrict__ gW, double *__restrict__ gb) {
-    const int entry = blockIdx.x * kThreads + threadIdx.x;
-    if (entry >= N * (K + 1)) return;
+    __shared__ double sums[8][33];
+    const int i = threadIdx.x & 31, y = threadIdx.x >> 5;
+    const int entry = blockIdx.x * 32 + i, total = N * (K + 1);
     double s = 0.0;
-    for (int y = 0; y < chunks; ++y) s += part[(size_t)y * N * (K + 1) + entry];
+    if (entry < total) {
+#pragma unroll 4
+        for (int c = y; c < chunks; c += 8) s += part[(size_t)c * total + entry];
+    }
+    sums[y][i] = s;
+    __syncthreads();
+    if (y != 0 || entry >= total) return;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) s += sums[k][i];
     const int c = entry / (K + 1), k = entry % (K + 1);
     if (k == K) gb[c] = s;
     else gW[(size_t)c * K + k] = s;
@@ -275,31 +358,50 @@ void bwd_records(const int2 *PQ, int Vb, int V, uint64_t *keys, int *flag, hipSt
     const int grid = std::min(8192, (V - Vb + kThreads - 1) / kThreads);
     hipLaunchKernelGGL(k_bwd_records, dim3(grid), dim3(kThreads), 0, st, PQ, Vb, V, keys, flag);
 }
-void bwd_pos(const uint32_t *vals, int n, int *pos, hipStream_t st) {
-    if (n <= 0) return;
-    const int grid = std::min(8192, (n + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL(k_bwd_pos, dim3(grid), dim3(kThreads), 0, st, vals, n, pos);
+void bwd_ranges(const uint64_t *skey, int nrec, int V, int2 *range, hipStream_t st) {
+    launch_fill64(reinterpret_cast<uint64_t *>(range), V, 0ull, st);
+    if (nrec <= 0) return;
+    const int grid = std::min(8192, (nrec + kThreads - 1) / kThreads);
+    hipLaunchKernelGGL(k_bwd_ranges, dim3(grid), dim3(kThreads), 0, st, skey, nrec, V, range);
+}
+static int depth_grid(int n) { return std::max(1, std::min(512, n / 2048)); }
+void bwd_depth_count(const uint32_t *DEP, int lw0, int Vs, int Ve, int *count, int *flag, hipStream_t st) {
+    if (Ve <= Vs) return;
+    hipLaunchKernelGGL(k_bwd_depth_count, dim3(depth_grid(Ve - Vs)), dim3(kThreads), 0, st, DEP, lw0, Vs, Ve, count,
+                       flag);
+}
+void bwd_depth_order(const uint32_t *DEP, int lw0, int Vs, int Ve, int *next, int *order, hipStream_t st) {
+    if (Ve <= Vs) return;
+    hipLaunchKernelGGL(k_bwd_depth_order, dim3(depth_grid(Ve - Vs)), dim3(kThreads), 0, st, DEP, lw0, Vs, Ve, next,
+                       order);
+}
+template <typename T, int G, int NC>
+static void pull_as(const BwdLayer<T> &L, const int *order, int n, hipStream_t st) {
+    const int per = kThreads / G, grid = std::min(8192, (n + per - 1) / per);
+    hipLaunchKernelGGL((k_bwd_pull<T, G, NC>), dim3(grid), dim3(kThreads), 0, st, L, order, n);
 }
 template <typename T>
-void bwd_step(const double *X, const double *Zs, const int2 *PQ, T *gx, T *gz, int D, int N, int ZS, int j, int Vb,
-              int V0, int S, const uint64_t *skey, int nrec, const int *pos, double *tt, T *gtt, int *flag,
-              hipStream_t st) {
-    if (S <= 0) return;
-    int grid = (S + 3) / 4;
-    grid = grid > 8192 ? 8192 : grid;
-    hipLaunchKernelGGL(k_bwd_child<T>, dim3(grid), dim3(kThreads), 0, st, X, Zs, PQ, gx, gz, D, N, ZS, j, V0, S, tt,
-                       gtt);
-    grid = (2 * S + 3) / 4;
-    grid = grid > 8192 ? 8192 : grid;
-    hipLaunchKernelGGL(k_bwd_parent<T>, dim3(grid), dim3(kThreads), 0, st, Zs, PQ, gx, gz, D, N, ZS, j, Vb, V0, S, skey,
-                       nrec, pos, tt, gtt, flag);
+void bwd_pull(const BwdLayer<T> &L, const int *order, int n, hipStream_t st) {
+    if (n <= 0) return;
+    // (a group also holds the D <= 16 coordinates)
+    if (L.N <= 16) pull_as<T, 16, 1>(L, order, n, st);
+    else if (L.N <= 32) pull_as<T, 32, 1>(L, order, n, st);
+    else if (L.N <= 64) pull_as<T, 64, 1>(L, order, n, st);
+    else if (L.N <= 128) pull_as<T, 64, 2>(L, order, n, st);
+    else pull_as<T, 64, 4>(L, order, n, st);
+}
+static int wg_tiles(int n) { return (n + kWgTile - 1) / kWgTile; }
+// Enough workgroups to fill the card (a chunk of 2048 vertices left 12 of them
+// to 25K vertices: 0.37 ms a layer), a chunk of at least two rounds of rows.
+int bwd_chunks(int Vs, int N, int K) {
+    const int tiles = wg_tiles(N) * wg_tiles(K);
+    return std::max(1, std::min((1024 + tiles - 1) / tiles, Vs / (2 * kWgRows)));
 }
 template <typename T>
 void bwd_layer(const T *gz, int ZS, const double *hin, int hstride, int relu, int Vs, int N, int K, const double *W,
                double *part, int chunks, double *gW, double *gb, T *gzp, int ZSp, hipStream_t st) {
-    const int entries = N * (K + 1);
-    const int gx = (entries + kThreads - 1) / kThreads;
-    const int tiles_c = (N + kWgTile - 1) / kWgTile, tiles_k = (K + 1 + kWgTile - 1) / kWgTile;
+    const int gx = (N * (K + 1) + 31) / 32;
+    const int tiles_c = wg_tiles(N), tiles_k = wg_tiles(K);
     hipLaunchKernelGGL(k_bwd_wgrad_tiled<T>, dim3(tiles_c * tiles_k, chunks), dim3(256), 0, st, gz, ZS, hin, hstride,
                        relu, Vs, N, K, tiles_k, part);
     hipLaunchKernelGGL(k_bwd_wreduce, dim3(gx), dim3(kThreads), 0, st, part, chunks, N, K, gW, gb);
@@ -311,10 +413,8 @@ void bwd_layer(const T *gz, int ZS, const double *hin, int hstride, int relu, in
 
 template void bwd_init<double>(const double *, double *, size_t, double *, size_t, hipStream_t);
 template void bwd_init<float>(const double *, float *, size_t, float *, size_t, hipStream_t);
-template void bwd_step<double>(const double *, const double *, const int2 *, double *, double *, int, int, int, int, int,
-                               int, int, const uint64_t *, int, const int *, double *, double *, int *, hipStream_t);
-template void bwd_step<float>(const double *, const double *, const int2 *, float *, float *, int, int, int, int, int,
-                              int, int, const uint64_t *, int, const int *, double *, float *, int *, hipStream_t);
+template void bwd_pull<double>(const BwdLayer<double> &, const int *, int, hipStream_t);
+template void bwd_pull<float>(const BwdLayer<float> &, const int *, int, hipStream_t);
 template void bwd_layer<double>(const double *, int, const double *, int, int, int, int, int, const double *, double *,
                                 int, double *, double *, double *, int, hipStream_t);
 template void bwd_layer<float>(const float *, int, const double *, int, int, int, int, int, const double *, double *,

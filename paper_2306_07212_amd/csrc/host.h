@@ -81,6 +81,7 @@ struct pcx_complex {
     bool taped = false;
     int ZS = 0, nsub = 0;
     int2 *PQ = nullptr;
+    uint32_t *DEP = nullptr;
     std::vector<double *> Zl;
     std::vector<int> layer_step0;
 };

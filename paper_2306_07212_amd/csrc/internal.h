@@ -106,6 +106,17 @@ struct StepGeom {
     int next;        // the neuron whose splitting edges the pairing also lists: j + 1, or -1 (none, or the layer's end)
 };
 
+// Tape word of a new vertex: its layer (the layer's first sign word), the neuron
+// that created it, and its depth: one more than the deeper of its parents,
+// where vertices from before the layer have depth 0. Within a layer a vertex's
+// children are all deeper than itself.
+__host__ __device__ inline uint32_t dep_word(int lw0, int j, int depth) {
+    return (uint32_t)lw0 << 18 | (uint32_t)j << 9 | (uint32_t)depth;
+}
+__host__ __device__ inline int dep_neuron(uint32_t w) { return (int)(w >> 9 & 511u); }
+__host__ __device__ inline int dep_depth(uint32_t w, int lw0) { return (int)(w >> 18) == lw0 ? (int)(w & 511u) : 0; }
+constexpr int kMaxDepth = kMaxWidth;  // a layer's steps
+
 // Log of one neuron step, written by its last kernel: counts at its start, its
 // split count, and the edge count after it.
 struct StepRec {
@@ -134,6 +145,7 @@ struct Bufs {
     int *CTR;         // [CTR_COUNT]
     const uint64_t *VALID;  // [Wd] 01-pattern at every valid entry
     int2 *PQ;         // [Vcap] (V+, V-) parents of each new vertex, when the tape is recorded (else null)
+    uint32_t *DEP;    // [Vcap] with PQ: the neuron that created the vertex and its depth (dep_word)
     StepRec *REC;     // [n_steps] per-step log (per-step path only; null in the batched kernel)
     uint64_t *LW;     // [V][8] the evaluated layer's sign words again, in 64-byte rows, for the
                       // layer-start scan (written by the evaluation when set; else null)
@@ -186,8 +198,10 @@ void launch_move_rows(const Bufs &b, const uint8_t *mark, const int *map, int V,
                       uint64_t *SG2, double *Z2, int2 *E2, int Enew, hipStream_t st);
 // result: *keys / *vals (K32a/VALa or K32b/VALb, by the pass count)
 void launch_sort(const Bufs &b, int n, hipStream_t st, const uint32_t **keys, const uint32_t **vals);
-// the same over 64-bit keys K64a / K64b, all bits (the exact pass)
-void launch_sort64(const Bufs &b, int n, hipStream_t st, const uint64_t **keys, const uint32_t **vals);
+// the same over 64-bit keys K64a / K64b: bits [8 first, 8 (first + passes)), all
+// of them for the exact pass
+void launch_sort64(const Bufs &b, int n, hipStream_t st, const uint64_t **keys, const uint32_t **vals, int first = 0,
+                   int passes = 8);
 // sort pairing (host-known counts): edges from E1 on, the edge count after the step into CTR_E[par ^ 1]
 void launch_pair(const Bufs &b, const StepGeom &g, int V0, int E1, int nslots, const uint32_t *keys,
                  const uint32_t *vals, hipStream_t st);
@@ -198,6 +212,8 @@ void launch_pair(const Bufs &b, const StepGeom &g, int V0, int E1, int nslots, c
 // covered; full: the largest grids). Returns the chunks of the next step's
 // list (its g.nlist).
 int launch_hash_pair(const Bufs &b, const StepGeom &g, int64_t slots, int64_t edges, bool full, hipStream_t st);
+// the tape words of a step's new vertices, where no hash pairing writes them
+void launch_tape_depths(const Bufs &b, const StepGeom &g, int S, hipStream_t st);
 // the exact pass of one step's pairing (after a pairing failure): every valid
 // key slot's 2-face sign-vector is rebuilt from its new vertex's row, sorted by
 // a 64-bit hash, and grouped by exact comparison of the rows; the pairs are
@@ -214,13 +230,30 @@ template <typename T>
 void bwd_init(const double *grad, T *gx, size_t n, T *gz, size_t nz, hipStream_t st);
 // the creation graph's (parent, child, side) records of the new vertices Vb .. V-1, unsorted
 void bwd_records(const int2 *PQ, int Vb, int V, uint64_t *keys, int *flag, hipStream_t st);
-// pos[vals[i]] = i: where each record sits after the sort
-void bwd_pos(const uint32_t *vals, int n, int *pos, hipStream_t st);
-// one step in reverse: each child's t and dL/dt, then each parent sums its children (in order)
+// range[P]: the first of parent P's records in the sorted order and the one past its last ((0, 0) if it has none)
+void bwd_ranges(const uint64_t *skey, int nrec, int V, int2 *range, hipStream_t st);
+// a layer's new vertices Vs .. Ve-1 by depth: count[d] (kMaxDepth + 1 entries, zero before) of each depth, then,
+// from the depths' first places next[d] (overwritten), the vertices in order[]
+void bwd_depth_count(const uint32_t *DEP, int lw0, int Vs, int Ve, int *count, int *flag, hipStream_t st);
+void bwd_depth_order(const uint32_t *DEP, int lw0, int Vs, int Ve, int *next, int *order, hipStream_t st);
+// the arrays of a layer's reverse pass
 template <typename T>
-void bwd_step(const double *X, const double *Zs, const int2 *PQ, T *gx, T *gz, int D, int N, int ZS, int j, int Vb,
-              int V0, int S, const uint64_t *skey, int nrec, const int *pos, double *tt, T *gtt, int *flag,
-              hipStream_t st);
+struct BwdLayer {
+    const double *X, *Z;    // coordinates; the layer's pre-activation rows (stride ZS)
+    const int2 *PQ;
+    const uint32_t *DEP;
+    const uint64_t *skey;   // sorted records, and each parent's range of them
+    const int2 *range;
+    int Vs, Ve, D, N, ZS;
+    T *gx, *gz;
+    double *tt;             // of each finished child: t of its splitting edge,
+    T *gp, *gq;             //   and what dL/dt adds to dL/dz of its V+ and V- parent
+};
+// vertices order[0..n) (null: 0..n-1) of one depth: each sums its children of the layer; new ones then get tt, gp, gq
+template <typename T>
+void bwd_pull(const BwdLayer<T> &L, const int *order, int n, hipStream_t st);
+// vertices per chunk of the weight gradient's partial sums, and their number
+int bwd_chunks(int Vs, int N, int K);
 template <typename T>
 void bwd_layer(const T *gz, int ZS, const double *hin, int hstride, int relu, int Vs, int N, int K, const double *W,
                double *part, int chunks, double *gW, double *gb, T *gzp, int ZSp, hipStream_t st);

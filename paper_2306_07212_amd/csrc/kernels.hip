@@ -1002,14 +1002,14 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(const K *__restrict__
     }
 }
 
-// passes of 8 bits over the low 8 * passes key bits; the first pass takes the
+// passes of 8 bits over the key bits from 8 * first on; the first pass takes the
 // slot ids as values
 template <typename K>
-static void sort_passes(K *ka, K *kb, uint32_t *va, uint32_t *vb, uint32_t *hist, int n, int passes, hipStream_t st,
-                        const K **keys, const uint32_t **vals) {
+static void sort_passes(K *ka, K *kb, uint32_t *va, uint32_t *vb, uint32_t *hist, int n, int first, int passes,
+                        hipStream_t st, const K **keys, const uint32_t **vals) {
     const int ntiles = (n + kSortTile - 1) / kSortTile;
     for (int pass = 0; n > 0 && pass < passes; ++pass) {
-        const int shift = 8 * pass;
+        const int shift = 8 * (first + pass);
         hipLaunchKernelGGL(k_sort_hist<K>, dim3(ntiles), dim3(kThreads), 0, st, ka, n, shift, hist, ntiles);
         hipLaunchKernelGGL(k_sort_scan, dim3(kSortBins), dim3(kThreads), 0, st, hist, ntiles);
         hipLaunchKernelGGL(k_sort_scatter<K>, dim3(ntiles), dim3(kThreads), 0, st, ka, pass == 0 ? nullptr : va, kb,
@@ -1022,12 +1022,12 @@ static void sort_passes(K *ka, K *kb, uint32_t *va, uint32_t *vb, uint32_t *hist
 }
 
 void launch_sort(const Bufs &b, int n, hipStream_t st, const uint32_t **keys, const uint32_t **vals) {
-    sort_passes<uint32_t>(b.K32a, b.K32b, b.VALa, b.VALb, b.HIST, n, kSortPasses, st, keys, vals);
+    sort_passes<uint32_t>(b.K32a, b.K32b, b.VALa, b.VALb, b.HIST, n, 0, kSortPasses, st, keys, vals);
 }
 
-// all 64 key bits (eight passes): the exact pass's sort
-void launch_sort64(const Bufs &b, int n, hipStream_t st, const uint64_t **keys, const uint32_t **vals) {
-    sort_passes<uint64_t>(b.K64a, b.K64b, b.VALa, b.VALb, b.HIST, n, 8, st, keys, vals);
+void launch_sort64(const Bufs &b, int n, hipStream_t st, const uint64_t **keys, const uint32_t **vals, int first,
+                   int passes) {
+    sort_passes<uint64_t>(b.K64a, b.K64b, b.VALa, b.VALb, b.HIST, n, first, passes, st, keys, vals);
 }
 
 // ------------------------------------------- step 5c: pair and connect
@@ -1133,6 +1133,26 @@ __device__ __forceinline__ void clear_table(const Bufs &b, const StepGeom &g) {
     if (!g.HTo) return;
     const uint32_t clear_n = (uint32_t)b.CTR[CTR_TUSED + (g.par ^ 1)];
     for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < clear_n; i += gridDim.x * kThreads) g.HTo[i] = 0ull;
+}
+
+// The workgroup's share of the tape words of the step's new vertices (their
+// parents are all older than the step).
+__device__ __forceinline__ void tape_depths(const Bufs &b, const StepGeom &g, int V0, int S) {
+    if (!b.PQ) return;
+    for (int x0 = V0 + blockIdx.x * kThreads + threadIdx.x; x0 < V0 + S; x0 += gridDim.x * kThreads) {
+        const int2 pq = b.PQ[x0];
+        b.DEP[x0] = dep_word(g.lw0, g.j, 1 + max(dep_depth(b.DEP[pq.x], g.lw0), dep_depth(b.DEP[pq.y], g.lw0)));
+    }
+}
+
+// the same alone (sort pairing)
+__global__ __launch_bounds__(kThreads) void k_tape_depths(Bufs b, StepGeom g) {
+    tape_depths(b, g, b.CTR[CTR_V + g.par], b.CTR[CTR_S]);
+}
+
+void launch_tape_depths(const Bufs &b, const StepGeom &g, int S, hipStream_t st) {
+    const int grid = std::max(1, std::min(1024, (S + kThreads - 1) / kThreads));
+    hipLaunchKernelGGL(k_tape_depths, dim3(grid), dim3(kThreads), 0, st, b, g);
 }
 
 // Sum over the workgroup (every thread gets it); s_w: one int per wave.
@@ -1338,6 +1358,7 @@ __global__ __launch_bounds__(kThreads) void k_pair_scan(Bufs b, StepGeom g, int 
     if (pair_blocked(b, g)) return;
     const int V0 = b.CTR[CTR_V + g.par], E0 = b.CTR[CTR_E + g.par], S = b.CTR[CTR_S];
     clear_table(b, g);
+    tape_depths(b, g, V0, S);
     const int nscan = (int)gridDim.x - np;
     if ((int)blockIdx.x < np) emit_chunk<true>(b, g, V0, E0, S, blockIdx.x, np, nscan, s_w);
     else scan_chunk<false>(b, g, E0 + S, blockIdx.x - np, nscan, s_w);
@@ -1350,6 +1371,7 @@ __global__ __launch_bounds__(kThreads) void k_count_scan(Bufs b, StepGeom g, int
     if (pair_blocked(b, g)) return;
     const int E0 = b.CTR[CTR_E + g.par], S = b.CTR[CTR_S], nslots = S * g.P;
     clear_table(b, g);
+    tape_depths(b, g, b.CTR[CTR_V + g.par], S);
     if ((int)blockIdx.x >= np) {
         scan_chunk<true>(b, g, E0 + S, blockIdx.x - np, (int)gridDim.x - np, s_w);
         return;
