@@ -62,26 +62,33 @@ __device__ __forceinline__ void cell_insert(const CellTable &T, uint64_t K, uint
     raise_flag(ctr, FLAG_BOUNDS);  // full: cannot happen at load factor <= 1/2
 }
 
-// The sign row of cell (edge, code) in the lanes of one wave: word it*64+lane
+template <int G>
+__device__ __forceinline__ uint64_t group_ballot(bool x, int gshift) {
+    const uint64_t m = __ballot(x);
+    return G == 64 ? m : (m >> gshift) & ((1ull << (G & 63)) - 1ull);
+}
+
+// The sign row of cell (edge, code) in the lanes of a group of G: word it*G+lane
 // for it = 0.. (uniform loop). Calls visit(it, w, live, row_word, zeros_all,
-// remaining_zeros, rank_of_first_zero) per iteration.
-template <class F>
+// remaining_zeros, rank_of_first_zero) per iteration. gshift: first lane of the
+// group in its wave.
+template <int G, class F>
 __device__ __forceinline__ void cell_row(const uint64_t *SG, const uint64_t *VALID, int Wd, int2 ab, uint32_t code,
-                                         int lane, F visit) {
+                                         int lane, int gshift, F visit) {
     int rank = 0;  // zeros of the edge before this iteration's words
-    for (int it = 0; it * 64 < Wd; ++it) {
-        const int w = it * 64 + lane;
+    for (int it = 0; it * G < Wd; ++it) {
+        const int w = it * G + lane;
         const bool live = w < Wd;
         uint64_t r = live ? (SG[(size_t)ab.x * Wd + w] | SG[(size_t)ab.y * Wd + w]) : 0ull;
         const uint64_t zm = live ? (~(r | (r >> 1)) & VALID[w]) : 0ull;
         const int zc = __popcll(zm);
         int mybase = 0;
-        uint64_t has = __ballot(zc != 0);
+        uint64_t has = group_ballot<G>(zc != 0, gshift);
         while (has) {
             const int sl = __builtin_ctzll(has);
             has &= has - 1;
             if (lane == sl) mybase = rank;
-            rank += __shfl(zc, sl, 64);
+            rank += __shfl(zc, sl, G);
         }
         uint64_t rem = 0, z = zm;
         for (int k = 0; z; ++k) {
@@ -95,13 +102,17 @@ __device__ __forceinline__ void cell_row(const uint64_t *SG, const uint64_t *VAL
     }
 }
 
-// One wave per k-cell: every parent (k+1)-cell goes into the table.
+// One group of G lanes per k-cell (G >= its parents): every parent (k+1)-cell
+// goes into the table. Bound: instructions per cell, so four cells share a wave
+// while rows are short (3-64-64-1, 5 words a row: 0.37 ms a level with a wave
+// per cell).
+template <int G>
 __global__ __launch_bounds__(kThreads) void k_cell_parents(const int2 *cells, int n, const int2 *EDG,
                                                           const uint64_t *SG, const uint64_t *VALID, int Wd, int V,
                                                           CellTable T, int *ctr) {
-    const int lane = threadIdx.x & 63;
-    const int waves = (gridDim.x * kThreads) >> 6;
-    for (int c = (blockIdx.x * kThreads + threadIdx.x) >> 6; c < n; c += waves) {
+    const int lane = threadIdx.x % G, gshift = (threadIdx.x & 63) / G * G;
+    const int groups = gridDim.x * (kThreads / G);
+    for (int c = (blockIdx.x * kThreads + threadIdx.x) / G; c < n; c += groups) {
         const int2 ec = cells ? cells[c] : make_int2(c, 0);
         const int2 ab = EDG[ec.x];
         if ((unsigned)ab.x >= (unsigned)V || (unsigned)ab.y >= (unsigned)V) {
@@ -112,20 +123,20 @@ __global__ __launch_bounds__(kThreads) void k_cell_parents(const int2 *cells, in
         // candidate `lane`: its word, that word of the cell row, its remaining zeros, all zeros, zero rank base
         uint64_t kf = 0, kz = 0, ka = 0;
         int kw = -1, kli = 0, kbase = 0, ktot = 0;
-        cell_row(SG, VALID, Wd, ab, (uint32_t)ec.y, lane,
+        cell_row<G>(SG, VALID, Wd, ab, (uint32_t)ec.y, lane, gshift,
                  [&](int it, int w, bool live, uint64_t r, uint64_t zm, uint64_t rem, int mybase) {
                      if (live) {
                          hsum += word_hash(w, r);
                          csum += word_check(w, r);
                      }
                      const int rc = __popcll(rem);
-                     uint64_t has = __ballot(rc != 0);
+                     uint64_t has = group_ballot<G>(rc != 0, gshift);
                      int srcl = lane;
                      bool mine = false;
                      while (has) {
                          const int sl = __builtin_ctzll(has);
                          has &= has - 1;
-                         const int c2 = __shfl(rc, sl, 64);
+                         const int c2 = __shfl(rc, sl, G);
                          const int keys = (it == 0 && sl == 0) ? c2 : 2 * c2;  // domain zeros only to +
                          if (lane >= ktot && lane < ktot + keys) {
                              srcl = sl;
@@ -134,20 +145,18 @@ __global__ __launch_bounds__(kThreads) void k_cell_parents(const int2 *cells, in
                          }
                          ktot += keys;
                      }
-                     const uint64_t f = __shfl(r, srcl, 64), rz = __shfl(rem, srcl, 64), az = __shfl(zm, srcl, 64);
-                     const int b0 = __shfl(mybase, srcl, 64);
+                     const uint64_t f = __shfl(r, srcl, G), rz = __shfl(rem, srcl, G), az = __shfl(zm, srcl, G);
+                     const int b0 = __shfl(mybase, srcl, G);
                      if (mine) {
                          kf = f;
                          kz = rz;
                          ka = az;
                          kbase = b0;
-                         kw = it * 64 + srcl;
+                         kw = it * G + srcl;
                      }
                  });
-        for (int o = 32; o > 0; o >>= 1) {
-            hsum += __shfl_xor(hsum, o, 64);
-            csum += __shfl_xor(csum, o, 64);
-        }
+        hsum = group_sum<G>(hsum);
+        csum = group_sum<G>(csum);
         if (lane < ktot && kw >= 0) {
             const uint64_t sg = (kw == 0 || (kli & 1) == 0) ? 1ull : 2ull;
             uint64_t z = kz;
@@ -178,21 +187,66 @@ struct TakeOrigin {
 };
 
 // sign rows of the given cells (every zero of their edge coded)
+template <int G>
 __global__ __launch_bounds__(kThreads) void k_cell_rows(const int2 *cells, int n, const int2 *EDG, const uint64_t *SG,
                                                        const uint64_t *VALID, int Wd, uint64_t *out) {
-    const int lane = threadIdx.x & 63;
-    const int waves = (gridDim.x * kThreads) >> 6;
-    for (int c = (blockIdx.x * kThreads + threadIdx.x) >> 6; c < n; c += waves) {
+    const int lane = threadIdx.x % G, gshift = (threadIdx.x & 63) / G * G;
+    const int groups = gridDim.x * (kThreads / G);
+    for (int c = (blockIdx.x * kThreads + threadIdx.x) / G; c < n; c += groups) {
         const int2 ec = cells[c];
         const int2 ab = EDG[ec.x];
-        cell_row(SG, VALID, Wd, ab, (uint32_t)ec.y, lane,
+        cell_row<G>(SG, VALID, Wd, ab, (uint32_t)ec.y, lane, gshift,
                  [&](int, int w, bool live, uint64_t r, uint64_t, uint64_t, int) {
                      if (live) out[(size_t)c * Wd + w] = r;
                  });
     }
 }
 
-int grid_for(int64_t waves) { return (int)std::max<int64_t>(1, std::min<int64_t>(65536, (waves + 3) / 4)); }
+int grid_for(int64_t groups, int G) {
+    const int per = kThreads / G;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(65536, (groups + per - 1) / per));
+}
+// lanes per cell: its words, and each of its up to 2(D - 1) parents, have a lane
+int cell_lanes(int D, int Wd) {
+    const int need = std::max(2 * (D - 1), Wd);
+    return need <= 16 ? 16 : need <= 32 ? 32 : 64;
+}
+
+// ---- the order of the regions
+//
+// Rows are ordered lexicographically by word. A region's entries are all + (01)
+// or - (10), so each neuron is one bit of the order, its words' entries from the
+// last to the first; the domain's word is the same in every row. Bits are packed
+// 64 to a key, and the keys sorted from the last to the first (stable radix
+// sorts of 8-bit digits), each time from the order so far.
+__global__ __launch_bounds__(kThreads) void k_region_keys(const uint64_t *__restrict__ rows, int n, int Wd, int w0,
+                                                          const uint32_t *__restrict__ order,
+                                                          uint64_t *__restrict__ keys) {
+    for (int i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads) {
+        const uint64_t *r = rows + (size_t)(order ? order[i] : (uint32_t)i) * Wd;
+        uint64_t k = 0;
+        for (int w = w0; w < w0 + 2; ++w) {
+            // the upper bit of every code, packed
+            uint64_t x = w < Wd ? r[w] >> 1 & 0x5555555555555555ull : 0ull;
+            x = (x | x >> 1) & 0x3333333333333333ull;
+            x = (x | x >> 2) & 0x0F0F0F0F0F0F0F0Full;
+            x = (x | x >> 4) & 0x00FF00FF00FF00FFull;
+            x = (x | x >> 8) & 0x0000FFFF0000FFFFull;
+            x = (x | x >> 16) & 0x00000000FFFFFFFFull;
+            k = k << 32 | x;
+        }
+        keys[i] = k;
+    }
+}
+
+// rows in order; one thread a word
+__global__ __launch_bounds__(kThreads) void k_region_gather(const uint64_t *__restrict__ rows, int n, int Wd,
+                                                            const uint32_t *__restrict__ order,
+                                                            uint64_t *__restrict__ out) {
+    const size_t total = (size_t)n * Wd;
+    for (size_t i = blockIdx.x * (size_t)kThreads + threadIdx.x; i < total; i += (size_t)gridDim.x * kThreads)
+        out[i] = rows[(size_t)order[i / Wd] * Wd + i % Wd];
+}
 
 // Runs the levels; counts[k] = number of k-cells, k = 0..D. With regions != null
 // the D-cells' (edge, codes) and keys are left in *regions / *rkeys (device,
@@ -233,8 +287,14 @@ int cells_run(const pcx_complex *cx, hipStream_t st, std::vector<int64_t> &count
         T.mask = (uint32_t)(tsz - 1);
         HIPCHK(hipMemsetAsync(T.key, 0, tsz * sizeof(unsigned long long), st));
         HIPCHK(hipMemsetAsync(T.chk, 0, tsz * sizeof(unsigned long long), st));
-        hipLaunchKernelGGL(k_cell_parents, dim3(grid_for(n)), dim3(kThreads), 0, st, level, (int)n, cx->EDG, cx->SG,
-                           valid, Wd, (int)cx->V, T, ctr);
+        const int G = cell_lanes(D, Wd);
+        auto parents = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(grid_for(n, G)), dim3(kThreads), 0, st, level, (int)n, cx->EDG, cx->SG, valid,
+                               Wd, (int)cx->V, T, ctr);
+        };
+        if (G == 16) parents(k_cell_parents<16>);
+        else if (G == 32) parents(k_cell_parents<32>);
+        else parents(k_cell_parents<64>);
         HIPCHK(hipGetLastError());
         // the (k+1)-cells, in table order
         hipLaunchKernelGGL(k_ccount<Occupied>, dim3(kChunks), dim3(kThreads), 0, st, Occupied{T.key}, (int)tsz, cnt);
@@ -324,20 +384,44 @@ int pcx_regions(const pcx_complex *cx, uint64_t *rows, int64_t *n, void *stream)
         reg = (int2 *)p;
         HIPCHK(hipStreamSynchronize(st));
     }
-    hipLaunchKernelGGL(k_cell_rows, dim3(grid_for(nr)), dim3(kThreads), 0, st, reg, (int)nr, cx->EDG, cx->SG, valid, Wd,
-                       drows);
+    const int G = cell_lanes(D, Wd);
+    auto fill = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid_for(nr, G)), dim3(kThreads), 0, st, reg, (int)nr, cx->EDG, cx->SG, valid, Wd,
+                           drows);
+    };
+    if (G == 16) fill(k_cell_rows<16>);
+    else if (G == 32) fill(k_cell_rows<32>);
+    else fill(k_cell_rows<64>);
     HIPCHK(hipGetLastError());
-    std::vector<uint64_t> h((size_t)nr * Wd);
-    HIPCHK(hipMemcpyAsync(h.data(), drows, h.size() * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
     // deterministic order: lexicographic by sign row (words from the first)
-    std::vector<int64_t> ord(nr);
-    std::iota(ord.begin(), ord.end(), 0);
-    std::sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) {
-        return std::lexicographical_compare(h.begin() + a * Wd, h.begin() + (a + 1) * Wd, h.begin() + b * Wd,
-                                            h.begin() + (b + 1) * Wd);
-    });
-    for (int64_t i = 0; i < nr; ++i) std::copy(h.begin() + ord[i] * Wd, h.begin() + (ord[i] + 1) * Wd, rows + i * Wd);
+    Bufs sb{};
+    if ((rc = ar.alloc(&p, (size_t)nr * sizeof(uint64_t)))) return rc;
+    sb.K64a = (uint64_t *)p;
+    if ((rc = ar.alloc(&p, (size_t)nr * sizeof(uint64_t)))) return rc;
+    sb.K64b = (uint64_t *)p;
+    if ((rc = ar.alloc(&p, (size_t)nr * sizeof(uint32_t)))) return rc;
+    sb.VALa = (uint32_t *)p;
+    if ((rc = ar.alloc(&p, (size_t)nr * sizeof(uint32_t)))) return rc;
+    sb.VALb = (uint32_t *)p;
+    if ((rc = ar.alloc(&p, (size_t)kSortBins * ((nr + kSortTile - 1) / kSortTile + 1) * sizeof(uint32_t)))) return rc;
+    sb.HIST = (uint32_t *)p;
+    if ((rc = ar.alloc(&p, (size_t)nr * Wd * sizeof(uint64_t)))) return rc;
+    uint64_t *sorted = (uint64_t *)p;
+    const int grid = (int)std::min<int64_t>(8192, (nr + kThreads - 1) / kThreads);
+    const uint32_t *order = nullptr;
+    for (int w = 1 + (Wd - 2) / 2 * 2; w >= 1; w -= 2) {
+        hipLaunchKernelGGL(k_region_keys, dim3(grid), dim3(kThreads), 0, st, drows, (int)nr, Wd, w, order, sb.K64a);
+        // the key's bytes in use: its low half is empty when the row ends with its first word
+        const uint64_t *sk = nullptr;
+        const int first = w + 1 < Wd ? 0 : 4;
+        launch_sort64(sb, (int)nr, st, &sk, &order, first, 8 - first, order != nullptr);
+        if (order == sb.VALb) std::swap(sb.VALa, sb.VALb);  // (the next sort reads the order so far)
+    }
+    const int gg = (int)std::min<int64_t>(8192, (nr * Wd + kThreads - 1) / kThreads);
+    hipLaunchKernelGGL(k_region_gather, dim3(gg), dim3(kThreads), 0, st, drows, (int)nr, Wd, order, sorted);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipMemcpyAsync(rows, sorted, (size_t)nr * Wd * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipStreamSynchronize(st));
     (void)keys;
     return PCX_OK;
 }

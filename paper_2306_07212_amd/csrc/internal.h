@@ -199,9 +199,9 @@ void launch_move_rows(const Bufs &b, const uint8_t *mark, const int *map, int V,
 // result: *keys / *vals (K32a/VALa or K32b/VALb, by the pass count)
 void launch_sort(const Bufs &b, int n, hipStream_t st, const uint32_t **keys, const uint32_t **vals);
 // the same over 64-bit keys K64a / K64b: bits [8 first, 8 (first + passes)), all
-// of them for the exact pass
+// of them for the exact pass; the values are the indexes, or (have_vals) VALa's
 void launch_sort64(const Bufs &b, int n, hipStream_t st, const uint64_t **keys, const uint32_t **vals, int first = 0,
-                   int passes = 8);
+                   int passes = 8, bool have_vals = false);
 // sort pairing (host-known counts): edges from E1 on, the edge count after the step into CTR_E[par ^ 1]
 void launch_pair(const Bufs &b, const StepGeom &g, int V0, int E1, int nslots, const uint32_t *keys,
                  const uint32_t *vals, hipStream_t st);

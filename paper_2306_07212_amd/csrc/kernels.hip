@@ -1003,16 +1003,17 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(const K *__restrict__
 }
 
 // passes of 8 bits over the key bits from 8 * first on; the first pass takes the
-// slot ids as values
+// slot ids as values, or (have_vals) those in va
 template <typename K>
 static void sort_passes(K *ka, K *kb, uint32_t *va, uint32_t *vb, uint32_t *hist, int n, int first, int passes,
-                        hipStream_t st, const K **keys, const uint32_t **vals) {
+                        hipStream_t st, const K **keys, const uint32_t **vals, bool have_vals = false) {
     const int ntiles = (n + kSortTile - 1) / kSortTile;
     for (int pass = 0; n > 0 && pass < passes; ++pass) {
         const int shift = 8 * (first + pass);
         hipLaunchKernelGGL(k_sort_hist<K>, dim3(ntiles), dim3(kThreads), 0, st, ka, n, shift, hist, ntiles);
         hipLaunchKernelGGL(k_sort_scan, dim3(kSortBins), dim3(kThreads), 0, st, hist, ntiles);
-        hipLaunchKernelGGL(k_sort_scatter<K>, dim3(ntiles), dim3(kThreads), 0, st, ka, pass == 0 ? nullptr : va, kb,
+        hipLaunchKernelGGL(k_sort_scatter<K>, dim3(ntiles), dim3(kThreads), 0, st, ka,
+                           pass == 0 && !have_vals ? nullptr : va, kb,
                            vb, n, shift, hist, ntiles);
         K *tk = ka; ka = kb; kb = tk;
         uint32_t *tv = va; va = vb; vb = tv;
@@ -1026,8 +1027,8 @@ void launch_sort(const Bufs &b, int n, hipStream_t st, const uint32_t **keys, co
 }
 
 void launch_sort64(const Bufs &b, int n, hipStream_t st, const uint64_t **keys, const uint32_t **vals, int first,
-                   int passes) {
-    sort_passes<uint64_t>(b.K64a, b.K64b, b.VALa, b.VALb, b.HIST, n, first, passes, st, keys, vals);
+                   int passes, bool have_vals) {
+    sort_passes<uint64_t>(b.K64a, b.K64b, b.VALa, b.VALb, b.HIST, n, first, passes, st, keys, vals, have_vals);
 }
 
 // ------------------------------------------- step 5c: pair and connect
