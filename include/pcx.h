@@ -260,7 +260,9 @@ int pcx_batch_tune(int32_t n, const pcx_mlp *const *mlps, const double *lo, cons
  * batched kernel; whatever arrives during a tick joins the next one. Larger
  * networks run on the per-step path in large_workers threads, each on its own
  * stream, overlapping with the ticks; so does a small network that would be
- * alone in its tick while a worker is free. A result is exactly the complex
+ * alone in its tick while a worker is free, and, while few requests wait, one
+ * that would hold its tick up (more than 12000 vertices predicted, or a layer
+ * wider than 64). A result is exactly the complex
  * pcx_extract returns for the same request. The server keeps the pcx_mlp
  * handle of a request until that request is released: the caller must not
  * free it before. Latency = completion - submission (host steady clock). */
