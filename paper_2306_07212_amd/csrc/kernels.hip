@@ -24,6 +24,22 @@ __device__ __forceinline__ bool step_blocked(const int *ctr, int step) {
     return ctr[CTR_FLAGS] != 0 || ctr[CTR_PFAIL] < step;
 }
 
+// The counters a per-step kernel starts from, read at once: a test of the flags
+// before the other loads would put another round trip to memory on the chain of
+// every launch. (The empty asm keeps the loads together, before the test.)
+struct StepCounters {
+    int flags, pfail, V0, E0, S;
+    __device__ __forceinline__ StepCounters(const int *ctr, int par)
+        : flags(ctr[CTR_FLAGS]), pfail(ctr[CTR_PFAIL]), V0(ctr[CTR_V + par]), E0(ctr[CTR_E + par]), S(ctr[CTR_S]) {
+        flags = __builtin_amdgcn_readfirstlane(flags);
+        pfail = __builtin_amdgcn_readfirstlane(pfail);
+        V0 = __builtin_amdgcn_readfirstlane(V0);
+        E0 = __builtin_amdgcn_readfirstlane(E0);
+        S = __builtin_amdgcn_readfirstlane(S);
+        asm volatile("" : "+s"(flags), "+s"(pfail), "+s"(V0), "+s"(E0), "+s"(S));
+    }
+};
+
 // --------------------------------------------------------- step 0: the box
 
 // 2^D corners (bit j of the corner id picks hi_j) and D 2^(D-1) edges between
@@ -701,49 +717,58 @@ __device__ __forceinline__ uint32_t table_size(int n) {
     return t;
 }
 
-// The chunks of the step's split list (SELTAB) scanned by the whole workgroup:
-// s_pre[c] = splits before chunk c, s_off[c] = its first entry less that.
-// Returns the step's split count. One gathered list (n == 1) takes no scan.
-__device__ __forceinline__ int list_scan(const Bufs &b, int n, int *s_pre, int *s_off, int *s_w) {
-    if (n == 1) return b.SELTAB[0].y;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    constexpr int kPer = kListMax / kThreads;
-    const int per = (n + kThreads - 1) / kThreads;
+// The chunks of the step's split list (SELTAB), read by load() and scanned by
+// the whole workgroup: s_pre[c] = splits before chunk c, s_off[c] = its first
+// entry less that. scan() returns the step's split count. One gathered list
+// (n == 1) takes no scan.
+struct ListScan {
+    static constexpr int kPer = kListMax / kThreads;
     int2 e[kPer];
-    int mine = 0;
+    int head;  // splits in the first chunk
+    __device__ __forceinline__ void load(const Bufs &b, int n) {
+        const int per = (n + kThreads - 1) / kThreads;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int c = t * per + i;
-        e[i] = i < per && c < n ? b.SELTAB[c] : make_int2(0, 0);
-        mine += e[i].y;
-    }
-    int incl = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += y;
-    }
-    if (lane == 63) s_w[wave] = incl;
-    __syncthreads();
-    int run = incl - mine, total = 0;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) {
-        const int x = s_w[w];
-        if (w < wave) run += x;
-        total += x;
-    }
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int c = t * per + i;
-        if (i < per && c < n) {
-            s_pre[c] = run;
-            s_off[c] = e[i].x - run;
-            run += e[i].y;
+        for (int i = 0; i < kPer; ++i) {
+            const int c = (int)threadIdx.x * per + i;
+            e[i] = i < per && c < n && n > 1 ? b.SELTAB[c] : make_int2(0, 0);
         }
+        head = b.SELTAB[0].y;
     }
-    __syncthreads();
-    return total;
-}
+    __device__ __forceinline__ int scan(int n, int *s_pre, int *s_off, int *s_w) const {
+        if (n == 1) return head;
+        const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+        const int per = (n + kThreads - 1) / kThreads;
+        int mine = 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) mine += e[i].y;
+        int incl = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        if (lane == 63) s_w[wave] = incl;
+        __syncthreads();
+        int run = incl - mine, total = 0;
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) {
+            const int x = s_w[w];
+            if (w < wave) run += x;
+            total += x;
+        }
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int c = t * per + i;
+            if (i < per && c < n) {
+                s_pre[c] = run;
+                s_off[c] = e[i].x - run;
+                run += e[i].y;
+            }
+        }
+        __syncthreads();
+        return total;
+    }
+};
 
 // place of split s in SPLE: in the last chunk that starts at or before it
 // (`head` splits in the first one, which starts at entry 0)
@@ -761,9 +786,12 @@ __device__ __forceinline__ int list_entry(int s, int n, int head, const int *s_p
 template <int G, int NC>
 __global__ __launch_bounds__(kThreads, 5) void k_split(Bufs b, StepGeom g) {
     __shared__ int s_pre[kListMax], s_off[kListMax], s_w[kThreads / 64];
-    if (step_blocked(b.CTR, g.step)) return;
-    const int V0 = b.CTR[CTR_V + g.par], E0 = b.CTR[CTR_E + g.par];
-    const int head = b.SELTAB[0].y, S = list_scan(b, g.nlist, s_pre, s_off, s_w);
+    ListScan list;
+    list.load(b, g.nlist);
+    const StepCounters ctr(b.CTR, g.par);
+    if (ctr.flags != 0 || ctr.pfail < g.step) return;  // (step_blocked)
+    const int V0 = ctr.V0, E0 = ctr.E0;
+    const int head = list.head, S = list.scan(g.nlist, s_pre, s_off, s_w);
     if (blockIdx.x == 0 && threadIdx.x == 0) b.CTR[CTR_S] = S;
     // every later kernel of the step writes within these bounds
     if ((int64_t)V0 + S > g.Vcap || (int64_t)E0 + (int64_t)S * g.D > g.Ecap || (int64_t)S * g.P > g.Kcap) {
@@ -1348,16 +1376,17 @@ __device__ __forceinline__ void emit_chunk(const Bufs &b, const StepGeom &g, int
 }
 
 // this step's split must not have failed its pairing (else the exact pass redoes it)
-__device__ __forceinline__ bool pair_blocked(const Bufs &b, const StepGeom &g) {
-    return b.CTR[CTR_FLAGS] || b.CTR[CTR_PFAIL] <= g.step;
+__device__ __forceinline__ bool pair_blocked(const StepCounters &c, const StepGeom &g) {
+    return c.flags != 0 || c.pfail <= g.step;
 }
 
 // Small steps: np emission workgroups, which count the owners before their
 // chunks themselves, then the scan's.
 __global__ __launch_bounds__(kThreads) void k_pair_scan(Bufs b, StepGeom g, int np) {
     __shared__ int s_w[kThreads / 64];
-    if (pair_blocked(b, g)) return;
-    const int V0 = b.CTR[CTR_V + g.par], E0 = b.CTR[CTR_E + g.par], S = b.CTR[CTR_S];
+    const StepCounters ctr(b.CTR, g.par);
+    if (pair_blocked(ctr, g)) return;
+    const int V0 = ctr.V0, E0 = ctr.E0, S = ctr.S;
     clear_table(b, g);
     tape_depths(b, g, V0, S);
     const int nscan = (int)gridDim.x - np;
@@ -1369,10 +1398,11 @@ __global__ __launch_bounds__(kThreads) void k_pair_scan(Bufs b, StepGeom g, int 
 // (SELCNT) from one coalesced read of the records, and the scan beside it.
 __global__ __launch_bounds__(kThreads) void k_count_scan(Bufs b, StepGeom g, int np) {
     __shared__ int s_w[kThreads / 64];
-    if (pair_blocked(b, g)) return;
-    const int E0 = b.CTR[CTR_E + g.par], S = b.CTR[CTR_S], nslots = S * g.P;
+    const StepCounters ctr(b.CTR, g.par);
+    if (pair_blocked(ctr, g)) return;
+    const int E0 = ctr.E0, S = ctr.S, nslots = S * g.P;
     clear_table(b, g);
-    tape_depths(b, g, b.CTR[CTR_V + g.par], S);
+    tape_depths(b, g, ctr.V0, S);
     if ((int)blockIdx.x >= np) {
         scan_chunk<true>(b, g, E0 + S, blockIdx.x - np, (int)gridDim.x - np, s_w);
         return;
@@ -1388,8 +1418,9 @@ __global__ __launch_bounds__(kThreads) void k_count_scan(Bufs b, StepGeom g, int
 // second launch: the emission, and the scan's matches packed beside it
 __global__ __launch_bounds__(kThreads) void k_pair_emit(Bufs b, StepGeom g, int np) {
     __shared__ int s_w[kThreads / 64];
-    if (pair_blocked(b, g)) return;
-    const int V0 = b.CTR[CTR_V + g.par], E0 = b.CTR[CTR_E + g.par], S = b.CTR[CTR_S];
+    const StepCounters ctr(b.CTR, g.par);
+    if (pair_blocked(ctr, g)) return;
+    const int V0 = ctr.V0, E0 = ctr.E0, S = ctr.S;
     if ((int)blockIdx.x < np) emit_chunk<false>(b, g, V0, E0, S, blockIdx.x, np, 1, s_w);
     else pack_chunk(b, E0 + S, blockIdx.x - np, (int)gridDim.x - np, s_w);
 }
