@@ -128,7 +128,8 @@ void pcx_mlp_free(pcx_mlp *mlp);
  * is small (at most 15000 vertices for D <= 2, 4200 for D = 3, 1800, 500 and
  * 120 for D = 4, 5 and 6) runs as a batch of one instead (one launch, the same
  * complex; PCX_NO_TINY=1 turns this off, PCX_TINY_VERTICES sets the threshold
- * for every D). */
+ * for every D); so does one with wider layers on the line (15000), or in the
+ * plane behind a first layer of at most 10 neurons (10000). */
 int pcx_extract(const pcx_mlp *mlp, const double *lo, const double *hi, const pcx_opts *opts,
                 pcx_complex **out);
 

@@ -510,24 +510,31 @@ struct Domain {
 //   D = 3:  2,717: 0.46, 0.62 / 0.48; 4,822: 0.74, 0.74 / 0.52
 //   D = 4:  1,250: 0.25, 0.40 / 0.28; 2,593: 0.44, 0.48 / 0.34
 //   D = 5:  1,047: 0.21, 0.33 / 0.22; D = 6: 789: 0.17, 0.29 / 0.18
-// (wider layers: the batched kernel's 256-thread workgroup took 2.8 ms for
-// 2-100-30-1, the per-step kernels 2.0 / 1.7).
+// Networks with a wider layer take the batched kernel's 256-thread workgroup where
+// few vertices arise for their steps, which cost it 5 us each and the per-step
+// kernels 11 / 9: on the line (1-204-204: 2.33 ms against 5.07 / 4.04), and in the
+// plane behind a first layer of few neurons (2-5-5-100, 1,378 vertices: 1.05, 1.55 /
+// 1.22; but 2-16-70, 2,289: 1.24, 1.31 / 1.07; 2-100-30, 5,960: 2.86, 2.09 / 1.74).
 double tiny_vertices(int D) {
     static const double limit[7] = {0.0, 15000.0, 15000.0, 4200.0, 1800.0, 500.0, 120.0};
     return D <= 6 ? limit[D] : 0.0;
+}
+double tiny_wide_vertices(const pcx_mlp *mlp) {
+    return mlp->D == 1 ? 15000.0 : mlp->D == 2 && mlp->widths[1] <= 10 ? 10000.0 : 0.0;
 }
 bool tiny_eligible(const pcx_mlp *mlp, const pcx_opts &o, int nsub) {
     const char *off = getenv("PCX_NO_TINY");
     if (off && off[0] == '1') return false;
     if (o.pairing != PCX_PAIR_HASH || o.prune || o.record_tape || o.timing || o.max_bytes) return false;
     if (mlp->D > kBatchMaxD || mlp->L > kBatchMaxLayers) return false;
-    int N = 0, Wd = 1;
+    int N = 0, Wd = 1, widest = 0;
     for (int l = 1; l <= nsub; ++l) {
-        if (mlp->widths[l] > kSmallWidth) return false;
+        if (mlp->widths[l] > kMaxWidth) return false;
+        widest = std::max(widest, mlp->widths[l]);
         N += mlp->widths[l];
         Wd += (mlp->widths[l] + 31) / 32;
     }
-    double limit = tiny_vertices(mlp->D);
+    double limit = widest <= kSmallWidth ? tiny_vertices(mlp->D) : tiny_wide_vertices(mlp);
     if (const char *v = getenv("PCX_TINY_VERTICES")) limit = atof(v);
     return Wd <= kBatchMaxWords && N > 0 && predict_vertices(mlp->D, N) <= limit;
 }
