@@ -251,12 +251,13 @@ __device__ __forceinline__ bool slot_owner(const Bufs &b, const StepGeom &g, int
 // (the same 2-face). check_rows: first verify that their perturbed sign rows
 // agree on every entry before the current neuron; check_hash: also compare the
 // stored 64-bit hashes (the hash table already matched them exactly). preA:
-// words wn .. wn+3 of sa's row, when the caller has loaded them already.
+// words wn .. wn+3 of sa's row (preB: of sb's), when the caller has loaded them already.
 // Returns the edge's first crossing in the layer (kNoCol: none).
 template <class M = GlobalMem>
 __device__ __forceinline__ int emit_pair(const Bufs &b, const StepGeom &g, int V0, int nslots, int sa, int sb,
                                           size_t out, bool check_hash = true, bool check_rows = true,
-                                          const uint64_t *preA = nullptr, const M &m = M()) {
+                                          const uint64_t *preA = nullptr, const M &m = M(),
+                                          const uint64_t *preB = nullptr) {
     if ((unsigned)sa >= (unsigned)nslots || (unsigned)sb >= (unsigned)nslots) {
         raise_flag(b.CTR, FLAG_BOUNDS);
         return kNoCol;
@@ -287,7 +288,8 @@ __device__ __forceinline__ int emit_pair(const Bufs &b, const StepGeom &g, int V
         for (int i = 0; i < 4; ++i) {
             const int w = w0 + i;
             const uint64_t a = preA && w0 == g.wn ? preA[i] : (w < g.lw1 ? Ra[w] : 0ull);
-            x[i] = w < g.lw1 ? (a ^ Rb[w]) & gt_mask(w, g.wn, g.bn, g.lw1) : 0ull;
+            const uint64_t bb = preB && w0 == g.wn ? preB[i] : (w < g.lw1 ? Rb[w] : 0ull);
+            x[i] = w < g.lw1 ? (a ^ bb) & gt_mask(w, g.wn, g.bn, g.lw1) : 0ull;
         }
 #pragma unroll
         for (int i = 3; i >= 0; --i)

@@ -1313,9 +1313,10 @@ __device__ __forceinline__ void emit_chunk(const Bufs &b, const StepGeom &g, int
     // one slot per thread: an owner's edge is a chain of dependent row loads,
     // so owners are spread over as many threads as possible. A slot's record,
     // its partner's, and its row words from the neuron on (where an owner's
-    // first-crossing search starts) are loaded together.
+    // first-crossing search starts) are loaded together, the partner's row words
+    // as soon as its slot is known (3-256-256-256: 9.27 -> 8.93 ms).
     int partner = -1;
-    uint64_t pre[4];
+    uint64_t pre[4], prb[4];
     auto load_slot = [&](int u) {
         partner = -1;
 #pragma unroll
@@ -1326,6 +1327,9 @@ __device__ __forceinline__ void emit_chunk(const Bufs &b, const StepGeom &g, int
         for (int i = 0; i < 4; ++i)
             if (g.wn + i < g.lw1) pre[i] = Ra[g.wn + i];
         partner = slot_partner(b, g, u, nslots);
+        const uint64_t *Rb = b.SG + (size_t)(V0 + max(partner, 0) / g.P) * g.Wd;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) prb[i] = partner > u && g.wn + i < g.lw1 ? Rb[g.wn + i] : 0ull;
         // a fresh record must be returned by the partner's; a valid slot must have one
         if (partner >= 0 ? slot_partner(b, g, partner, nslots) != u : b.PINFO[u] != kNoInfo)
             raise_pair_flag(b.CTR, FLAG_RUN, g.step);
@@ -1352,7 +1356,7 @@ __device__ __forceinline__ void emit_chunk(const Bufs &b, const StepGeom &g, int
         int total;
         const int pos = E1 + run + block_rank(own, total, s_w);
         int col = kNoCol;
-        if (own) col = emit_pair(b, g, V0, nslots, u, partner, (size_t)pos, false, g.verify != 0, pre);
+        if (own) col = emit_pair(b, g, V0, nslots, u, partner, (size_t)pos, false, g.verify != 0, pre, GlobalMem(), prb);
         run += total;
         if (g.next >= 0) {
             const bool hit = own && col == g.next;
