@@ -93,64 +93,6 @@ __global__ __launch_bounds__(kThreads) void k_gemm(Bufs b, int ZS, const double 
     gemm_tile(b, ZS, in, in_stride, relu, V, K, N, Wt, bias, Wd, lw0, blockIdx.x * kGemmRows, hs, ws);
 }
 
-// The same evaluation for a narrow layer (N <= kGemvMaxN outputs, e.g. the
-// output neuron): one vertex per thread, 512 rows per workgroup, the rows
-// staged through LDS in chunks of kGemvK (64-byte row pieces: small chunks,
-// 18 KB of LDS per workgroup, keep many workgroups' loads in flight),
-// and the same sequential fma chain over k per output as gemm_tile, so every
-// evaluation kernel rounds alike. Weights are read at uniform addresses. In
-// place as above: a thread reads its whole row before it writes it.
-constexpr int kGemvMaxN = 8, kGemvRows = 512, kGemvK = 8;
-__global__ __launch_bounds__(kGemvRows) void k_gemv(Bufs b, int ZS, const double *in, int in_stride, int relu, int V,
-                                                     int K, int N, const double *__restrict__ Wt,
-                                                     const double *__restrict__ bias, int Wd, int lw0) {
-    __shared__ double hs[kGemvRows][kGemvK + 1];
-    const int t = threadIdx.x;
-    const int v0 = blockIdx.x * kGemvRows, v = v0 + t;
-    double acc[kGemvMaxN];
-#pragma unroll
-    for (int n = 0; n < kGemvMaxN; ++n) acc[n] = 0.0;
-    for (int k0 = 0; k0 < K; k0 += kGemvK) {
-        __syncthreads();  // the previous chunk has been read
-#pragma unroll
-        for (int i = 0; i < kGemvK; ++i) {
-            // element idx of the chunk: row idx / kGemvK, column idx % kGemvK
-            const int idx = t + kGemvRows * i, r = idx / kGemvK, k = idx % kGemvK;
-            double h = 0.0;
-            if (v0 + r < V && k0 + k < K) {
-                h = in[(size_t)(v0 + r) * in_stride + k0 + k];
-                if (relu) h = h > 0.0 ? h : 0.0;
-            }
-            hs[r][k] = h;
-        }
-        __syncthreads();
-        const int kc = min(kGemvK, K - k0);
-        for (int kk = 0; kk < kc; ++kk) {
-            const double h = hs[t][kk];
-#pragma unroll
-            for (int n = 0; n < kGemvMaxN; ++n)
-                if (n < N) acc[n] = fma(h, Wt[(size_t)(k0 + kk) * N + n], acc[n]);
-        }
-    }
-    if (v >= V) return;
-    uint32_t pos = 0, neg = 0;
-    int zero = 0;
-#pragma unroll
-    for (int n = 0; n < kGemvMaxN; ++n) {
-        if (n < N) {
-            const double z = acc[n] + bias[n];
-            b.Z[(size_t)v * ZS + n] = z;
-            zero |= (z == 0.0);
-            pos |= (uint32_t)(z > 0.0) << n;
-            neg |= (uint32_t)(z < 0.0) << n;
-        }
-    }
-    const uint64_t cw = codes_of(pos, neg);
-    b.SG[(size_t)v * Wd + lw0] = cw;
-    if (b.LW) b.LW[(size_t)v * 8] = cw;
-    if (zero) raise_flag(b.CTR, FLAG_ZERO_SIGN);
-}
-
 // ---- rows of an evaluation in spatial order
 //
 // Vertices that lie close together share most of the previous layer's dead
@@ -241,7 +183,7 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_scatter(const double *__res
     for (int v = v0 + t; v < v1; v += kBinThreads) perm[atomicAdd(&h[bin_of(X + (size_t)v * D, g, D)], 1)] = v;
 }
 
-// The same evaluation on the matrix cores (N > kGemvMaxN, finite weights). A
+// The same evaluation on the matrix cores (finite weights). A
 // workgroup takes 32 rows; its 4 waves are CW blocks of 16 CT columns and 4 / CW
 // bands of 16 RT rows, a wave RT x CT tiles of the FP64 16x16x4 MFMA (lane l of a
 // tile holds rows l/16 + 4i, column l%16, i = 0..3). A chain of these MFMAs
@@ -460,11 +402,6 @@ void launch_gemm(const Bufs &b, int ZS, const double *in, int in_stride, int rel
                  const double *Wt, const double *bias, int Wd, int lw0, bool finite, hipStream_t st,
                  const EvalGrid *grid) {
     if (V <= 0) return;
-    if (N <= kGemvMaxN) {
-        hipLaunchKernelGGL(k_gemv, dim3((V + kGemvRows - 1) / kGemvRows), dim3(kGemvRows), 0, st, b, ZS, in, in_stride,
-                           relu, V, K, N, Wt, bias, Wd, lw0);
-        return;
-    }
     if (!finite || K > kMaxWidth) {
         const int blocks = (V + kGemmRows - 1) / kGemmRows;
         hipLaunchKernelGGL(k_gemm, dim3(blocks), dim3(kThreads), 0, st, b, ZS, in, in_stride, relu, V, K, N, Wt, bias,
@@ -485,7 +422,10 @@ void launch_gemm(const Bufs &b, int ZS, const double *in, int in_stride, int rel
         hipLaunchKernelGGL(kernel, dim3((V + kEvalRows - 1) / kEvalRows), dim3(kEvalThreads), 0, st, b, ZS, in,
                            in_stride, relu, V, K, N, Wt, bias, Wd, lw0, perm);
     };
-    // (column blocks as narrow as the layer allows: a wave of a wider one would sit idle)
+    // (column blocks as narrow as the layer allows: a wave of a wider one would
+    // sit idle; a layer of one neuron is bound by reading its rows: 0.67M rows of
+    // 64 took 0.15 ms by one thread a row and take the same here, 55K rows of 200
+    // 0.12 ms and 0.03)
     if (N <= 64) run(k_gemm_mfma<2, 2, 1>);
     else if (N <= 128) run(k_gemm_mfma<4, 2, 2>);
     else run(k_gemm_mfma<4, 4, 2>);
