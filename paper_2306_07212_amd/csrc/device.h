@@ -190,12 +190,14 @@ __device__ __forceinline__ void hash_insert(const Bufs &b, const StepGeom &g, ui
     raise_flag(b.CTR, FLAG_BOUNDS);  // table full: cannot happen at load factor <= 1/2
 }
 
-// partner of valid key slot u from its record (-1: no fresh record)
-__device__ __forceinline__ int slot_partner(const Bufs &b, const StepGeom &g, int u, int nslots) {
-    const uint64_t r = b.PART[u];
+// partner of a valid key slot from its record (-1: no fresh record)
+__device__ __forceinline__ int record_partner(uint64_t r, int step, int nslots) {
     const uint32_t p1 = (uint32_t)r;
-    if ((uint32_t)(r >> 32) != (uint32_t)(g.step + 1) || p1 == 0u || p1 - 1u >= (uint32_t)nslots) return -1;
+    if ((uint32_t)(r >> 32) != (uint32_t)(step + 1) || p1 == 0u || p1 - 1u >= (uint32_t)nslots) return -1;
     return (int)(p1 - 1u);
+}
+__device__ __forceinline__ int slot_partner(const Bufs &b, const StepGeom &g, int u, int nslots) {
+    return record_partner(b.PART[u], g.step, nslots);
 }
 
 // Where a step keeps its key slots, its 2-face table and the edges' next
