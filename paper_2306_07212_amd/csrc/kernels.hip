@@ -423,9 +423,9 @@ void launch_gemm(const Bufs &b, int ZS, const double *in, int in_stride, int rel
                            in_stride, relu, V, K, N, Wt, bias, Wd, lw0, perm);
     };
     // (column blocks as narrow as the layer allows: a wave of a wider one would
-    // sit idle; a layer of one neuron is bound by reading its rows: 0.67M rows of
-    // 64 took 0.15 ms by one thread a row and take the same here, 55K rows of 200
-    // 0.12 ms and 0.03)
+    // sit idle. A layer of one neuron is bound by reading its rows: one thread a
+    // row took 0.195 ms for all layers of 2-200-200-1 with its output, this 0.105;
+    // 0.260 and 0.267 for 3-64-64-64-1)
     if (N <= 64) run(k_gemm_mfma<2, 2, 1>);
     else if (N <= 128) run(k_gemm_mfma<4, 2, 2>);
     else run(k_gemm_mfma<4, 4, 2>);
@@ -729,9 +729,12 @@ __global__ __launch_bounds__(kThreads, 5) void k_split(Bufs b, StepGeom g) {
     ListScan list;
     list.load(b, g.nlist);
     const StepCounters ctr(b.CTR, g.par);
-    if (ctr.flags != 0 || ctr.pfail < g.step) return;  // (step_blocked)
     const int V0 = ctr.V0, E0 = ctr.E0;
     const int head = list.head, S = list.scan(g.nlist, s_pre, s_off, s_w);
+    // (step_blocked, tested past the scan's barriers: a step that finds the storage
+    // too small raises its flag in this very launch, and waves of one workgroup may
+    // read it differently; those that see it and those that compute it then agree)
+    if (ctr.flags != 0 || ctr.pfail < g.step) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) b.CTR[CTR_S] = S;
     // every later kernel of the step writes within these bounds
     if ((int64_t)V0 + S > g.Vcap || (int64_t)E0 + (int64_t)S * g.D > g.Ecap || (int64_t)S * g.P > g.Kcap) {
@@ -1324,9 +1327,16 @@ __device__ __forceinline__ void emit_chunk(const Bufs &b, const StepGeom &g, int
     }
 }
 
-// this step's split must not have failed its pairing (else the exact pass redoes it)
-__device__ __forceinline__ bool pair_blocked(const StepCounters &c, const StepGeom &g) {
-    return c.flags != 0 || c.pfail <= g.step;
+// this step's split must not have failed its pairing (else the exact pass redoes
+// it). The emission raises these flags itself, so the waves of a workgroup may
+// read them differently: the first wave's answer is everyone's, as no wave may be
+// missing at the barriers that follow.
+__device__ __forceinline__ bool pair_blocked(const StepCounters &c, const StepGeom &g, int *s_w) {
+    if (threadIdx.x == 0) s_w[0] = c.flags != 0 || c.pfail <= g.step;
+    __syncthreads();
+    const bool blocked = s_w[0] != 0;
+    __syncthreads();  // s_w may be written
+    return blocked;
 }
 
 // Small steps: np emission workgroups, which count the owners before their
@@ -1334,7 +1344,7 @@ __device__ __forceinline__ bool pair_blocked(const StepCounters &c, const StepGe
 __global__ __launch_bounds__(kThreads) void k_pair_scan(Bufs b, StepGeom g, int np) {
     __shared__ int s_w[kThreads / 64];
     const StepCounters ctr(b.CTR, g.par);
-    if (pair_blocked(ctr, g)) return;
+    if (pair_blocked(ctr, g, s_w)) return;
     const int V0 = ctr.V0, E0 = ctr.E0, S = ctr.S;
     clear_table(b, g);
     tape_depths(b, g, V0, S);
@@ -1353,7 +1363,7 @@ __global__ __launch_bounds__(kThreads) void k_pair_scan(Bufs b, StepGeom g, int 
 __global__ __launch_bounds__(kThreads) void k_count_scan(Bufs b, StepGeom g, int np) {
     __shared__ int s_w[kThreads / 64];
     const StepCounters ctr(b.CTR, g.par);
-    if (pair_blocked(ctr, g)) return;
+    if (pair_blocked(ctr, g, s_w)) return;
     const int E0 = ctr.E0, S = ctr.S, nslots = S * g.P;
     clear_table(b, g);
     tape_depths(b, g, ctr.V0, S);
@@ -1382,7 +1392,7 @@ __global__ __launch_bounds__(kThreads) void k_count_scan(Bufs b, StepGeom g, int
 __global__ __launch_bounds__(kThreads) void k_pair_emit(Bufs b, StepGeom g, int np) {
     __shared__ int s_w[kThreads / 64];
     const StepCounters ctr(b.CTR, g.par);
-    if (pair_blocked(ctr, g)) return;
+    if (pair_blocked(ctr, g, s_w)) return;
     const int V0 = ctr.V0, E0 = ctr.E0, S = ctr.S;
     if ((int)blockIdx.x < np) emit_chunk<false>(b, g, V0, E0, S, blockIdx.x, np, 1, s_w);
     else pack_chunk(b, E0 + S, blockIdx.x - np, (int)gridDim.x - np, s_w);
