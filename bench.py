@@ -129,8 +129,8 @@ def host_cpu():
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "traffic.json")
 KERNEL_SOURCES = ["kernels.hip", "device.h", "internal.h"]
 # kernel name prefix -> family (the per-step path's kernels)
-KERNEL_FAMILY = {"pcx::k_gemm": "gemm", "pcx::k_next_all": "next", "pcx::k_sel_": "select",
-                 "pcx::k_split": "split", "pcx::k_sort_": "sort", "pcx::k_pair": "pair", "pcx::k_hpair_": "pair"}
+KERNEL_FAMILY = {"pcx::k_gemm": "gemm", "pcx::k_bin_": "gemm", "pcx::k_next_all": "next", "pcx::k_sel_": "select",
+                 "pcx::k_split": "split", "pcx::k_sort_": "sort", "pcx::k_pair": "pair", "pcx::k_count_scan": "pair"}
 
 
 def kernels_sha256():

@@ -336,8 +336,8 @@ int pcx_extract_into(const pcx_mlp *mlp, const double *lo, const double *hi, con
  * arithmetic of the reverse pass: PCX_F64 or PCX_F32 (results still FP64).
  * Each new vertex x0 = x_p + t (x_q - x_p), t = z_p / (z_p - z_q) of its
  * splitting edge (Sec. 4.2.1) is differentiated exactly as the forward pass
- * computed it; every vertex sums its children's contributions in child order
- * (no atomics), so the gradients are bit-identical from run to run. The call
+ * computed it; every vertex sums its children's contributions from the youngest
+ * child on (no atomics), so the gradients are bit-identical from run to run. The call
  * returns when the gradients are complete. */
 #define PCX_F64 0
 #define PCX_F32 1
