@@ -267,7 +267,9 @@ def form_batched(args, pcx, wl, torch):
     k_med = float(np.median(kms)) / 1e3
     achieved = b8 / k_med / 1e9
     roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": achieved / HBM_PEAK_GBS, "bytes_per_launch": b8, "kernel": "pcx::k_batch",
+            "frac": achieved / HBM_PEAK_GBS, "bytes_per_launch": b8,
+            # (layers of up to 64 neurons: the small-network kernel under the default schedule)
+            "kernel": "pcx::k_small" if (tuned["split_lanes"], tuned["select_items"]) == (16, 16) else "pcx::k_batch",
             "launches_per_step": 1, "avg_launch_us": k_med * 1e6, "traffic": None,
             "bytes_rule": "scope-table count summed over every network's steps; the launch also evaluates "
                           "every layer (FP64 MFMA for layers of up to 64 neurons, not in the count)"}
@@ -802,6 +804,9 @@ def main():
         if f == "gemm":
             fam_roof[f]["TFLOP_per_s"] = flops / s_ / 1e12
             fam_roof[f]["mfma_frac"] = flops / s_ / 1e12 / FP64_PEAK_TFLOPS
+            fam_roof[f]["note"] = ("every product of the layers counted; columns that the ReLU makes exactly zero in "
+                                   "all 32 rows of a workgroup are left out, so this is no rate of the matrix cores "
+                                   "(profiles/counters_plain_3x256.md has their busy cycles)")
         if f == "pair":
             fam_roof[f]["note"] = ("12 B per key slot and 25 B per pair (edge, next crossing, one sign word of each "
                                    "new vertex), and the next neuron's compaction (2 B per edge, 4 B per splitting "
