@@ -1285,8 +1285,7 @@ int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad,
     Bufs sb{};
     int2 *range = nullptr;
     int *order = nullptr, *depths = nullptr;
-    double *tt = nullptr;
-    T *gp = nullptr, *gq = nullptr;
+    BwdChild<T> *child = nullptr;
     const uint64_t *skey = nullptr;
     constexpr int kDepths = kMaxDepth + 1;
     std::vector<int> lw(nsub + 1, 1), Vstart(nsub + 1, (int)cx->V);
@@ -1313,12 +1312,8 @@ int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad,
         order = (int *)p;
         if ((rc = ar.alloc(&p, (size_t)nsub * kDepths * sizeof(int)))) return rc;
         depths = (int *)p;
-        if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(double)))) return rc;
-        tt = (double *)p;
-        if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(T)))) return rc;
-        gp = (T *)p;
-        if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(T)))) return rc;
-        gq = (T *)p;
+        if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(BwdChild<T>)))) return rc;
+        child = (BwdChild<T> *)p;
         // each layer's new vertices by depth
         HIPCHK(hipMemsetAsync(depths, 0, (size_t)nsub * kDepths * sizeof(int), st));
         for (int l = 0; l < nsub; ++l)
@@ -1356,7 +1351,7 @@ int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad,
         const int Vs = Vstart[l];
         if (Vstart[l + 1] > Vs) {
             BwdLayer<T> L{cx->X, cx->Zl[l], cx->PQ, cx->DEP, skey, range, Vs, Vstart[l + 1], D, N, ZS,
-                          gx, gz, tt, gp, gq};
+                          gx, gz, child};
             for (int d = kDepths - 1; d >= 1; --d)
                 bwd_pull<T>(L, order + place[(size_t)l * kDepths + d], count[(size_t)l * kDepths + d], st);
             bwd_pull<T>(L, nullptr, Vs, st);  // depth 0: the vertices from before the layer

@@ -107,13 +107,15 @@ __global__ __launch_bounds__(kThreads) void k_bwd_depth_order(const uint32_t *__
 // k G + c). First what its children of the layer add, youngest first:
 //   dL/dx_v += s dL/dx0,  dL/dZ_v[c] += s dL/dZ0[c]  (c != j),
 // s = 1 - t for the V+ parent and t for the V- parent, and to dL/dz_v of the
-// child's neuron j its share of dL/dt (gp or gq). Its gradients are then
-// complete (its children's were: they are deeper), so a new vertex gets t of its
-// splitting edge, dL/dt from its coordinates and every carried pre-activation
-// but its own neuron's, and the shares
-//   gp = dL/dt * -z_q / (z_p - z_q)^2,  gq = dL/dt * z_p / (z_p - z_q)^2.
-// Bound: the latency of the chain record -> child's row, so kAhead children's
-// loads are in flight at once.
+// child's neuron j its share of dL/dt, f dL/dt, with f = dt/dz:
+//   -z_q / (z_p - z_q)^2 for the V+ parent, z_p / (z_p - z_q)^2 for the V- parent.
+// Every term is one fused multiply-add in T (the two factors are selected, not
+// the product: a rounded product put the FP32 gradients half as far again from
+// FP64). The vertex's gradients are then complete (its children's were: they are
+// deeper), so a new vertex gets its child's record: t of its splitting edge, dL/dt
+// from its coordinates and every carried pre-activation but its own neuron's, and
+// both f. Bound: the latency of the chain list -> child's record and row, so
+// kAhead children's loads are in flight at once.
 template <typename T, int G, int NC>
 __global__ __launch_bounds__(kThreads) void k_bwd_pull(BwdLayer<T> L, const int *__restrict__ order, int n) {
     constexpr int kAhead = 4;
@@ -136,7 +138,7 @@ __global__ __launch_bounds__(kThreads) void k_bwd_pull(BwdLayer<T> L, const int 
         bool more = true;
         for (int r = own.y - 1; r >= own.x && more; r -= kAhead) {
             int child[kAhead], jn[kAhead];
-            T s[kAhead], gs[kAhead], cx[kAhead], cz[kAhead][NC];
+            T s[kAhead], f[kAhead], gt[kAhead], cx[kAhead], cz[kAhead][NC];
             bool live[kAhead];
 #pragma unroll
             for (int a = 0; a < kAhead; ++a) {
@@ -146,9 +148,10 @@ __global__ __launch_bounds__(kThreads) void k_bwd_pull(BwdLayer<T> L, const int 
                 more = more && child[a] >= L.Vs;
                 if (!live[a]) child[a] = v;  // (a row that is there; not used)
                 const bool side = key & 1u;
-                const double t = L.tt[child[a]];
-                s[a] = side ? (T)t : (T)(1.0 - t);
-                gs[a] = side ? L.gq[child[a]] : L.gp[child[a]];
+                const BwdChild<T> rec = L.child[child[a]];
+                s[a] = side ? (T)rec.t : (T)(1.0 - rec.t);
+                f[a] = side ? rec.fq : rec.fp;
+                gt[a] = rec.gt;
                 jn[a] = dep_neuron(L.DEP[child[a]]);
             }
 #pragma unroll
@@ -162,11 +165,11 @@ __global__ __launch_bounds__(kThreads) void k_bwd_pull(BwdLayer<T> L, const int 
             for (int a = 0; a < kAhead; ++a) {
                 if (!live[a]) continue;
                 any = true;
-                ax += s[a] * cx[a];
+                ax = fma(s[a], cx[a], ax);
 #pragma unroll
                 for (int k = 0; k < NC; ++k) {
-                    const int c = k * G + lane;
-                    az[k] += c == jn[a] ? gs[a] : s[a] * cz[a][k];
+                    const bool own_col = k * G + lane == jn[a];
+                    az[k] = fma(own_col ? f[a] : s[a], own_col ? gt[a] : cz[a][k], az[k]);
                 }
             }
         }
@@ -186,15 +189,13 @@ __global__ __launch_bounds__(kThreads) void k_bwd_pull(BwdLayer<T> L, const int 
 #pragma unroll
         for (int k = 0; k < NC; ++k) {
             const int c = k * G + lane;
-            if (c < L.N && c != j) gt += az[k] * (T)(L.Z[q * L.ZS + c] - L.Z[p * L.ZS + c]);
+            if (c < L.N && c != j) gt = fma(az[k], (T)(L.Z[q * L.ZS + c] - L.Z[p * L.ZS + c]), gt);
         }
 #pragma unroll
         for (int o = G / 2; o > 0; o >>= 1) gt += __shfl_xor(gt, o, G);
         if (lane == 0) {
             const double inv = 1.0 / (den * den);
-            L.tt[v] = zp / den;
-            L.gp[v] = gt * (T)(-zq * inv);
-            L.gq[v] = gt * (T)(zp * inv);
+            L.child[v] = BwdChild<T>{zp / den, gt, (T)(-zq * inv), (T)(zp * inv)};
         }
     }
 }

@@ -236,6 +236,12 @@ void bwd_ranges(const uint64_t *skey, int nrec, int V, int2 *range, hipStream_t 
 // from the depths' first places next[d] (overwritten), the vertices in order[]
 void bwd_depth_count(const uint32_t *DEP, int lw0, int Vs, int Ve, int *count, int *flag, hipStream_t st);
 void bwd_depth_order(const uint32_t *DEP, int lw0, int Vs, int Ve, int *next, int *order, hipStream_t st);
+// of a finished new vertex: t of its splitting edge, dL/dt, and dt/dz of its V+ and V- parent
+template <typename T>
+struct BwdChild {
+    double t;
+    T gt, fp, fq;
+};
 // the arrays of a layer's reverse pass
 template <typename T>
 struct BwdLayer {
@@ -246,10 +252,9 @@ struct BwdLayer {
     const int2 *range;
     int Vs, Ve, D, N, ZS;
     T *gx, *gz;
-    double *tt;             // of each finished child: t of its splitting edge,
-    T *gp, *gq;             //   and what dL/dt adds to dL/dz of its V+ and V- parent
+    BwdChild<T> *child;     // by vertex
 };
-// vertices order[0..n) (null: 0..n-1) of one depth: each sums its children of the layer; new ones then get tt, gp, gq
+// vertices order[0..n) (null: 0..n-1) of one depth: each sums its children of the layer; new ones then get their record
 template <typename T>
 void bwd_pull(const BwdLayer<T> &L, const int *order, int n, hipStream_t st);
 // vertices per chunk of the weight gradient's partial sums, and their number

@@ -57,3 +57,98 @@ def test_tape_of_a_sort_paired_extraction_gives_the_same_gradients():
     m.close()
     assert np.allclose(got[0][0], got[1][0], rtol=0, atol=1e-12)
     assert rel(got[0][1], got[1][1]) < 1e-8
+
+
+def _reverse_on_the_line(w, b, grad, lo, hi, fused):
+    """dL/db and dL/dw of a one-layer network on [lo, hi] in FP32 by the same sums: every vertex takes its children
+    from the youngest on, one term each, fused (one rounding) or not; a term's product is exact in FP64."""
+    N, f4 = len(w), np.float32
+    G = 16 if N <= 16 else 32 if N <= 32 else 64
+
+    def mac(a, x, acc):
+        p = np.float64(f4(a)) * np.float64(f4(x))
+        return f4(p + np.float64(acc)) if fused else f4(f4(p) + f4(acc))
+
+    X, Z, par, neuron = [lo, hi], [w * lo + b, w * hi + b], [None, None], [-1, -1]
+    line = [0, 1]  # vertices along the line
+    for j in range(N):
+        for i in range(len(line) - 1):
+            p, q = line[i], line[i + 1]
+            if (Z[p][j] > 0) == (Z[q][j] > 0):
+                continue
+            if Z[p][j] < 0:
+                p, q = q, p  # p = V+
+            t = Z[p][j] / (Z[p][j] - Z[q][j])
+            z = Z[p] + t * (Z[q] - Z[p])
+            z[j] = 0.0
+            X.append(X[p] + t * (X[q] - X[p]))
+            Z.append(z)
+            par.append((p, q, t))
+            neuron.append(j)
+            line.insert(i + 1, len(X) - 1)
+            break
+    V = len(X)
+    gx, gz = grad[:V].astype(f4), np.zeros((V, N), f4)
+    kids, rec = [[] for _ in range(V)], [None] * V
+    for v in range(2, V):
+        kids[par[v][0]].append((v, 0))
+        kids[par[v][1]].append((v, 1))
+    for v in range(V - 1, -1, -1):
+        for c, side in reversed(kids[v]):
+            t, gt, fs = rec[c]
+            s = f4(t) if side else f4(1.0 - t)
+            gx[v] = mac(s, gx[c], gx[v])
+            for k in range(N):
+                own = k == neuron[c]
+                gz[v, k] = mac(fs[side] if own else s, gt if own else gz[c, k], gz[v, k])
+        if v < 2:
+            continue
+        p, q, t = par[v]
+        lanes = np.zeros(G, f4)
+        lanes[0] = mac(gx[v], X[q] - X[p], f4(0))
+        for k in range(N):
+            if k != neuron[v]:
+                lanes[k] = mac(gz[v, k], Z[q][k] - Z[p][k], lanes[k])
+        o = G // 2
+        while o:
+            lanes = lanes + lanes[np.arange(G) ^ o]
+            o //= 2
+        zp, zq = Z[p][neuron[v]], Z[q][neuron[v]]
+        inv = 1.0 / ((zp - zq) * (zp - zq))
+        rec[v] = (t, lanes[0], (f4(-zq * inv), f4(zp * inv)))
+    return np.array([f4(gz[0, k] + gz[1, k]) for k in range(N)]), V
+
+
+@pytest.mark.parametrize("N", [16, 32, 64])
+def test_fp32_sums_round_once_a_term(N):
+    """On the line every value of the FP32 reverse pass can be followed on the host. With fused terms the library's
+    gradients are those bits (all but the few where FP64 stands in for the fused operation or a stored value differs
+    in its last place); sums whose products are rounded by themselves agree in far fewer entries."""
+    import torch
+    from paper_2306_07212_amd import pcx
+    same = {True: 0, False: 0}
+    total = 0
+    for seed in range(8):
+        net, box = wl.he_mlp([1, N, 1], [95, N, seed]), wl.cube(1)
+        m = pcx.MLP.from_net(net)
+        cx = pcx.extract(m, box.lo, box.hi, record_tape=True)
+        V = cx.info().V
+        grad = np.random.default_rng([96, seed]).standard_normal(V)
+        g = torch.from_numpy(grad).cuda()
+        gW = [torch.empty(w.shape, dtype=torch.float64, device="cuda") for w in net.W]
+        gb = [torch.empty(x.shape, dtype=torch.float64, device="cuda") for x in net.b]
+        pcx.backward(m, cx, g.data_ptr(), [t.data_ptr() for t in gW], [t.data_ptr() for t in gb], pcx.PCX_F32,
+                     torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        got = gb[0].cpu().numpy()
+        cx.close()
+        m.close()
+        for fused in same:
+            want, n = _reverse_on_the_line(net.W[0][:, 0], net.b[0], grad, float(box.lo[0]), float(box.hi[0]), fused)
+            assert n == V
+            live = want != 0.0
+            same[fused] += int((got[live] == want[live]).sum())
+            total += int(live.sum()) if fused else 0
+    print(f"[bwd] 1-{N}-1: {same[True]} of {total} entries as with fused terms, {same[False]} without", flush=True)
+    assert total > 4 * N and same[True] >= 0.98 * total
+    assert same[False] < 0.8 * total  # (the two can be told apart)
