@@ -393,10 +393,14 @@ void bwd_pull(const BwdLayer<T> &L, const int *order, int n, hipStream_t st) {
 }
 static int wg_tiles(int n) { return (n + kWgTile - 1) / kWgTile; }
 // Enough workgroups to fill the card (a chunk of 2048 vertices left 12 of them
-// to 25K vertices: 0.37 ms a layer), a chunk of at least two rounds of rows.
+// to 25K vertices: 0.37 ms a layer), a chunk of at least two rounds of rows; and,
+// as a chunk's rows are summed in the gradient's own arithmetic and only the
+// chunks in FP64, no longer chunks than that for layers of many tiles: 2048 rows
+// up to half a million vertices, then a 256th of them.
 int bwd_chunks(int Vs, int N, int K) {
     const int tiles = wg_tiles(N) * wg_tiles(K);
-    return std::max(1, std::min((1024 + tiles - 1) / tiles, Vs / (2 * kWgRows)));
+    const int fill = std::min((1024 + tiles - 1) / tiles, Vs / (2 * kWgRows));
+    return std::max({1, fill, std::min(256, Vs / 2048)});
 }
 template <typename T>
 void bwd_layer(const T *gz, int ZS, const double *hin, int hstride, int relu, int Vs, int N, int K, const double *W,
