@@ -16,6 +16,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "batch.h"
@@ -1267,64 +1268,70 @@ template <typename T>
 int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad, double *const *gW, double *const *gb,
                   hipStream_t st) {
     const int D = cx->D, ZS = cx->ZS, nsub = cx->nsub;
+    const int Vb = cx->n_steps > 0 ? (int)cx->steps[0] : (int)cx->V;
+    const int nrec = 2 * (int)(cx->V - Vb);
+    constexpr int kDepths = kMaxDepth + 1;
+    std::vector<int> lw(nsub + 1, 1), Vstart(nsub + 1, (int)cx->V);
+    size_t part_n = 0, prev_n = 0;
+    for (int l = 0; l < nsub; ++l) {
+        const int N = mlp->widths[l + 1], K = mlp->widths[l];
+        lw[l + 1] = lw[l] + (N + 31) / 32;
+        Vstart[l] = (int)cx->steps[(size_t)cx->layer_step0[l] * 4];
+        part_n = std::max(part_n, (size_t)bwd_chunks(Vstart[l], N, K) * N * (K + 1));
+        if (l > 0) prev_n = std::max(prev_n, (size_t)Vstart[l] * ZS);
+    }
+    // Everything the pass needs, before its first launch. Two arrays of gradient
+    // rows take turns: a layer's start has fewer vertices than its end. The sort's
+    // storage serves again after it (the records' values are not needed, and one of
+    // the two key arrays is free), so besides the rows a pass holds 56 bytes per new
+    // vertex and 8 per vertex.
     Arena ar;
     int rc;
     void *p;
-    int *dflag;
-    if ((rc = ar.alloc(&p, sizeof(int)))) return rc;
-    dflag = (int *)p;
+    auto take = [&](auto *&q, size_t n) {
+        rc = ar.alloc(&p, n * sizeof(*q));
+        q = (std::remove_reference_t<decltype(q)>)p;
+        return rc;
+    };
+    int *dflag = nullptr, *depths = nullptr;
+    T *gx = nullptr, *gz = nullptr, *gzp = nullptr;
+    double *part = nullptr;
+    Bufs sb{};
+    BwdChild<T> *child = nullptr;
+    static_assert(sizeof(BwdChild<T>) % sizeof(uint64_t) == 0, "whole words of the key array");
+    // (the records come in child order and the sort is stable: only the parents' bits are sorted)
+    int key_bytes = 1;
+    while (key_bytes < 4 && (cx->V >> (8 * key_bytes)) != 0) ++key_bytes;
+    if (take(dflag, 1) || take(gx, (size_t)cx->V * D) || take(gz, (size_t)cx->V * ZS) || take(gzp, prev_n) ||
+        take(part, part_n))
+        return rc;
+    if (nrec > 0) {
+        // (after the sort VALa holds the order by depth, VALb each parent's range of records)
+        uint64_t *&sorted = key_bytes % 2 == 0 ? sb.K64a : sb.K64b, *&spare = key_bytes % 2 == 0 ? sb.K64b : sb.K64a;
+        if (take(sorted, nrec) ||
+            take(spare, std::max((size_t)nrec, (size_t)(cx->V - Vb) * sizeof(BwdChild<T>) / sizeof(uint64_t))) ||
+            take(sb.VALa, nrec) || take(sb.VALb, 2 * (size_t)cx->V) ||
+            take(sb.HIST, (size_t)kSortBins * ((nrec + kSortTile - 1) / kSortTile + 1)) ||
+            take(depths, (size_t)nsub * kDepths))
+            return rc;
+        child = reinterpret_cast<BwdChild<T> *>(spare);
+    }
     HIPCHK(hipMemsetAsync(dflag, 0, sizeof(int), st));
-    if ((rc = ar.alloc(&p, (size_t)cx->V * D * sizeof(T)))) return rc;
-    T *gx = (T *)p;
-    if ((rc = ar.alloc(&p, (size_t)cx->V * ZS * sizeof(T)))) return rc;
-    T *gz = (T *)p;
     bwd_init<T>(grad, gx, (size_t)cx->V * D, gz, (size_t)cx->V * ZS, st);
     // every parent's children in increasing order: one sort of (parent, child, side) records
-    const int Vb = cx->n_steps > 0 ? (int)cx->steps[0] : (int)cx->V;
-    const int nrec = 2 * (int)(cx->V - Vb);
-    Bufs sb{};
-    int2 *range = nullptr;
-    int *order = nullptr, *depths = nullptr;
-    BwdChild<T> *child = nullptr;
+    int2 *range = reinterpret_cast<int2 *>(sb.VALb);
+    int *order = reinterpret_cast<int *>(sb.VALa);
     const uint64_t *skey = nullptr;
-    constexpr int kDepths = kMaxDepth + 1;
-    std::vector<int> lw(nsub + 1, 1), Vstart(nsub + 1, (int)cx->V);
-    for (int l = 0; l < nsub; ++l) {
-        lw[l + 1] = lw[l] + (mlp->widths[l + 1] + 31) / 32;
-        Vstart[l] = (int)cx->steps[(size_t)cx->layer_step0[l] * 4];
-    }
     std::vector<int> count((size_t)nsub * kDepths, 0), place((size_t)nsub * kDepths, 0);
     if (nrec > 0) {
-        if ((rc = ar.alloc(&p, (size_t)nrec * sizeof(uint64_t)))) return rc;
-        sb.K64a = (uint64_t *)p;
-        if ((rc = ar.alloc(&p, (size_t)nrec * sizeof(uint64_t)))) return rc;
-        sb.K64b = (uint64_t *)p;
-        if ((rc = ar.alloc(&p, (size_t)nrec * sizeof(uint32_t)))) return rc;
-        sb.VALa = (uint32_t *)p;
-        if ((rc = ar.alloc(&p, (size_t)nrec * sizeof(uint32_t)))) return rc;
-        sb.VALb = (uint32_t *)p;
-        if ((rc = ar.alloc(&p, (size_t)kSortBins * ((nrec + kSortTile - 1) / kSortTile + 1) * sizeof(uint32_t))))
-            return rc;
-        sb.HIST = (uint32_t *)p;
-        if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(int2)))) return rc;
-        range = (int2 *)p;
-        if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(int)))) return rc;
-        order = (int *)p;
-        if ((rc = ar.alloc(&p, (size_t)nsub * kDepths * sizeof(int)))) return rc;
-        depths = (int *)p;
-        if ((rc = ar.alloc(&p, (size_t)cx->V * sizeof(BwdChild<T>)))) return rc;
-        child = (BwdChild<T> *)p;
         // each layer's new vertices by depth
         HIPCHK(hipMemsetAsync(depths, 0, (size_t)nsub * kDepths * sizeof(int), st));
         for (int l = 0; l < nsub; ++l)
             bwd_depth_count(cx->DEP, lw[l], Vstart[l], Vstart[l + 1], depths + l * kDepths, dflag, st);
         HIPCHK(hipMemcpyAsync(count.data(), depths, count.size() * sizeof(int), hipMemcpyDeviceToHost, st));
-        // (the records come in child order and the sort is stable: only the parents' bits are sorted)
-        int bytes = 1;
-        while (bytes < 4 && (cx->V >> (8 * bytes)) != 0) ++bytes;
         bwd_records(cx->PQ, Vb, (int)cx->V, sb.K64a, dflag, st);
         const uint32_t *svals = nullptr;
-        launch_sort64(sb, nrec, st, &skey, &svals, 4, bytes);
+        launch_sort64(sb, nrec, st, &skey, &svals, 4, key_bytes);
         bwd_ranges(skey, nrec, (int)cx->V, range, st);
         HIPCHK(hipGetLastError());
         HIPCHK(hipStreamSynchronize(st));
@@ -1350,27 +1357,18 @@ int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad,
         const int N = mlp->widths[l + 1], K = mlp->widths[l];
         const int Vs = Vstart[l];
         if (Vstart[l + 1] > Vs) {
-            BwdLayer<T> L{cx->X, cx->Zl[l], cx->PQ, cx->DEP, skey, range, Vs, Vstart[l + 1], D, N, ZS,
+            BwdLayer<T> L{cx->X, cx->Zl[l], cx->PQ, cx->DEP, skey, range, Vs, Vstart[l + 1], Vb, D, N, ZS,
                           gx, gz, child};
             for (int d = kDepths - 1; d >= 1; --d)
                 bwd_pull<T>(L, order + place[(size_t)l * kDepths + d], count[(size_t)l * kDepths + d], st);
             bwd_pull<T>(L, nullptr, Vs, st);  // depth 0: the vertices from before the layer
             HIPCHK(hipGetLastError());
         }
-        const int chunks = bwd_chunks(Vs, N, K);
-        if ((rc = ar.alloc(&p, (size_t)chunks * N * (K + 1) * sizeof(double)))) return rc;
-        double *part = (double *)p;
-        T *gzp = nullptr;
-        if (l > 0) {
-            if ((rc = ar.alloc(&p, (size_t)Vs * ZS * sizeof(T)))) return rc;
-            gzp = (T *)p;
-        }
         const double *hin = l == 0 ? cx->X : cx->Zl[l - 1];
-        bwd_layer<T>(gz, ZS, hin, l == 0 ? D : ZS, l > 0 ? 1 : 0, Vs, N, K, mlp->Wr[l], part, chunks, gW[l], gb[l],
-                     gzp, ZS, st);
+        bwd_layer<T>(gz, ZS, hin, l == 0 ? D : ZS, l > 0 ? 1 : 0, Vs, N, K, mlp->Wr[l], part, bwd_chunks(Vs, N, K), gW[l],
+                     gb[l], l > 0 ? gzp : nullptr, ZS, st);
         HIPCHK(hipGetLastError());
-        // (the rows of the layers above stay allocated until the stream is done with them)
-        if (gzp) gz = gzp;
+        std::swap(gz, gzp);
     }
     int hflag = 0;
     HIPCHK(hipMemcpyAsync(&hflag, dflag, sizeof(int), hipMemcpyDeviceToHost, st));

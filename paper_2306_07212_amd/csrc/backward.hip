@@ -146,9 +146,9 @@ __global__ __launch_bounds__(kThreads) void k_bwd_pull(BwdLayer<T> L, const int 
                 child[a] = (int)((uint32_t)key >> 1);
                 live[a] = r - a >= own.x && child[a] >= L.Vs && child[a] < L.Ve;
                 more = more && child[a] >= L.Vs;
-                if (!live[a]) child[a] = v;  // (a row that is there; not used)
+                if (!live[a]) child[a] = L.Ve - 1;  // (a new vertex that is there; not used)
                 const bool side = key & 1u;
-                const BwdChild<T> rec = L.child[child[a]];
+                const BwdChild<T> rec = L.child[child[a] - L.Vb];
                 s[a] = side ? (T)rec.t : (T)(1.0 - rec.t);
                 f[a] = side ? rec.fq : rec.fp;
                 gt[a] = rec.gt;
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kThreads) void k_bwd_pull(BwdLayer<T> L, const int 
         for (int o = G / 2; o > 0; o >>= 1) gt += __shfl_xor(gt, o, G);
         if (lane == 0) {
             const double inv = 1.0 / (den * den);
-            L.child[v] = BwdChild<T>{zp / den, gt, (T)(-zq * inv), (T)(zp * inv)};
+            L.child[v - L.Vb] = BwdChild<T>{zp / den, gt, (T)(-zq * inv), (T)(zp * inv)};
         }
     }
 }

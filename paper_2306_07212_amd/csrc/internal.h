@@ -250,9 +250,9 @@ struct BwdLayer {
     const uint32_t *DEP;
     const uint64_t *skey;   // sorted records, and each parent's range of them
     const int2 *range;
-    int Vs, Ve, D, N, ZS;
+    int Vs, Ve, Vb, D, N, ZS;  // the layer's new vertices Vs .. Ve-1; Vb: the first new vertex of all
     T *gx, *gz;
-    BwdChild<T> *child;     // by vertex
+    BwdChild<T> *child;     // of vertex Vb + i
 };
 // vertices order[0..n) (null: 0..n-1) of one depth: each sums its children of the layer; new ones then get their record
 template <typename T>

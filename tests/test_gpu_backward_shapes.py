@@ -152,3 +152,37 @@ def test_fp32_sums_round_once_a_term(N):
     print(f"[bwd] 1-{N}-1: {same[True]} of {total} entries as with fused terms, {same[False]} without", flush=True)
     assert total > 4 * N and same[True] >= 0.98 * total
     assert same[False] < 0.8 * total  # (the two can be told apart)
+
+
+@pytest.mark.parametrize("precision,size", [("PCX_F64", 8), ("PCX_F32", 4)])
+def test_backward_holds_the_rows_of_two_layers(precision, size):
+    """Device memory of one backward of a network of many layers: the rows of two layers, the coordinates' gradients,
+    56 bytes per new vertex and 16 per vertex, and the partial sums (one layer's). Every block is rounded up to a
+    MiB; the library keeps them in its pool, so what the call took is what is missing after it."""
+    import torch
+    from paper_2306_07212_amd import pcx
+    net, box = wl.he_mlp([3, 64, 2, 2, 2, 2, 2, 2, 1], [97, 8]), wl.cube(3)
+    m = pcx.MLP.from_net(net)
+    cx = pcx.extract(m, box.lo, box.hi, include_output=True, record_tape=True)
+    V = cx.info().V
+    ZS, n = 64, V - int(cx.steps()[0, 0])
+    rng = np.random.default_rng(98)
+    g = torch.from_numpy(rng.standard_normal((V, 3))).cuda()
+    gW = [torch.empty(w.shape, dtype=torch.float64, device="cuda") for w in net.W]
+    gb = [torch.empty(x.shape, dtype=torch.float64, device="cuda") for x in net.b]
+    torch.cuda.synchronize()
+    pcx.cache_trim()
+    before = torch.cuda.mem_get_info()[0]
+    pcx.backward(m, cx, g.data_ptr(), [t.data_ptr() for t in gW], [t.data_ptr() for t in gb], getattr(pcx, precision),
+                 torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    held = before - torch.cuda.mem_get_info()[0]
+    pcx.cache_trim()
+    part = 1024 * 64 * 65 * 8  # (at most 1024 chunks of a layer's entries)
+    rows = V * ZS * size
+    room = 2 * rows + V * 3 * size + 56 * n + 16 * V + part + 16 * (2 << 20)
+    print(f"[bwd] {V} vertices, {precision}: {held / 2**20:.0f} MiB held, {room / 2**20:.0f} allowed, a layer's rows "
+          f"{rows / 2**20:.0f}", flush=True)
+    assert held <= room
+    cx.close()
+    m.close()
