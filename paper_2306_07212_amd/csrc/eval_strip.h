@@ -55,8 +55,8 @@ __device__ __noinline__ void eval_mfma(double *Zo_, uint64_t *SGo_, uint64_t *LW
         // four k-steps of 4 per round, each with its own operand registers: a
         // step's operands for the next round are loaded right after its MFMAs
         // issue, three steps ahead of their use, as raw bits from clamped
-        // in-bounds addresses; the zeros past K (weights) and the ReLU are
-        // applied when the step is used, so no load waits on a condition
+        // in-bounds addresses; the zeros past K and the ReLU are applied when the
+        // step is used, so no load waits on a condition
         uint64_t ar[4], br[4][CT];
         auto load = [&](int k0, uint64_t &a, uint64_t *bw) {
             const int k = k0 + q, kc = k < K ? k : K - 1;
@@ -76,7 +76,8 @@ __device__ __noinline__ void eval_mfma(double *Zo_, uint64_t *SGo_, uint64_t *LW
             for (int st = 0; st < 4; ++st) {
                 const bool kin = k0 + 4 * st + q < K;
                 const double h = __builtin_bit_cast(double, ar[st]);
-                const double af = relu ? (h > 0.0 ? h : 0.0) : h;
+                // (0 past K also here: an input that is infinite would make the zero weights' products NaN)
+                const double af = relu ? (kin && h > 0.0 ? h : 0.0) : h;
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) {
                     const uint64_t m = (kin && ct * 16 + r < N) ? ~0ull : 0ull;

@@ -35,3 +35,24 @@ def test_small_network_kernel_equals_the_per_step_kernels(monkeypatch, widths):
                 assert a.shape == b.shape and np.array_equal(a, b), f"{widths} schedule {sched} network {i}"
         bt.close()
     m.close()
+
+
+@pytest.mark.parametrize("widths", [[4, 5, 3, 1], [2, 17, 3, 1], [3, 16, 3, 1]])
+def test_an_infinite_neuron_stays_out_of_the_others(monkeypatch, widths):
+    """A first layer without crossings whose last neuron is infinite (an infinite bias): the second layer's are then
+    infinite too, by the signs of their weights, and every vertex keeps them; the padding of the evaluation's inner
+    dimension (K = 5, 17; 16 has none) must not turn them into NaN."""
+    from paper_2306_07212_amd import pcx
+    D, K, N = widths[0], widths[1], widths[2]
+    W = [np.full((K, D), 0.01), np.ones((N, K)) * np.array([1.0, -1.0, 1.0])[:, None], np.ones((1, N))]
+    b = [np.ones(K), np.zeros(N), np.zeros(1)]
+    b[0][K - 1] = np.inf
+    m, box = pcx.MLP(widths, W, b), wl.cube(D)
+    for off in ("0", "1"):
+        monkeypatch.setenv("PCX_NO_TINY", off)
+        cx = pcx.extract(m, box.lo, box.hi)
+        X, SG, Ed = cx.copy()
+        cx.close()
+        assert len(X) == 2**D and len(Ed) == D * 2 ** (D - 1)
+        assert np.all(SG[:, -1] == 0b011001), f"{widths} PCX_NO_TINY={off}"  # +, -, + from bit 0 on
+    m.close()
