@@ -1304,10 +1304,15 @@ __device__ __forceinline__ void emit_chunk(const Bufs &b, const StepGeom &g, int
         int total;
         const int pos = E1 + run + block_rank(own, total, s_w);
         int col = kNoCol;
-        if (own) col = emit_pair(b, g, V0, nslots, u, partner, (size_t)pos, false, g.verify != 0, pre, GlobalMem(), prb);
+        // (where faces share a table word, more slots than half can name a larger
+        // one, and the step asked for room for half: such a step is paired again, so
+        // an edge past the storage is left out)
+        const bool fits = pos < g.Ecap;
+        if (own && fits)
+            col = emit_pair(b, g, V0, nslots, u, partner, (size_t)pos, false, g.verify != 0, pre, GlobalMem(), prb);
         run += total;
         if (g.next >= 0) {
-            const bool hit = own && col == g.next;
+            const bool hit = own && fits && col == g.next;
             const int at = block_rank(hit, total, s_w);
             if (hit)
                 b.SPLE[E1 + first + listed + at] = make_int4(pos, V0 + u / g.P, V0 + partner / g.P, 0);

@@ -178,3 +178,27 @@ def test_step_with_more_key_slots_than_24_bits_name(pcx):
     cx.close()
     m.close()
     assert np.array_equal(steps, s2)
+
+
+@pytest.mark.parametrize("widths,seed,incl", NETS[1:5])
+def test_collisions_in_storage_without_slack(pcx, monkeypatch, widths, seed, incl):
+    """Nearly every slot of a step names the one that came first, so up to all but one of them may look like a pair's
+    owner, twice the edges that the step asked room for. In storage of exactly the sizes that an earlier extraction of
+    the same network reached (2-bit hashes from the second one on), and in storage grown step by step, the emission
+    stays inside it and the exact pass gives the same arrays."""
+    monkeypatch.setenv("PCX_NO_TINY", "1")
+    monkeypatch.setenv("PCX_NO_GRAPH", "1")
+    m, box = pcx.MLP.from_net(wl.he_mlp(widths, seed)), wl.cube(widths[0])
+    got = []
+    for env in ({}, {"PCX_DEBUG_HASH_BITS": "2"}, {"PCX_DEBUG_HASH_BITS": "2", "PCX_SMALL_START": "1"}):
+        with monkeypatch.context() as mp:
+            for k, v in env.items():
+                mp.setenv(k, v)
+            cx = pcx.extract(m, box.lo, box.hi, include_output=incl)
+        got.append((*cx.copy(), cx.steps()))
+        assert bool(env) == (cx.info().exact_steps > 0)
+        cx.close()
+    m.close()
+    for other in got[1:]:
+        for a, b in zip(other, got[0]):
+            assert a.shape == b.shape and np.array_equal(a, b)
