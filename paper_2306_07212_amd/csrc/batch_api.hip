@@ -87,12 +87,48 @@ int launch_events(hipEvent_t &a, hipEvent_t &b) {
     return PCX_OK;
 }
 
+// Storage of a batched launch: one arena per workgroup, for its largest network,
+// and the output pool.
+struct BatchRoom {
+    size_t vbytes, abytes;
+    int ecap, kcap;
+    uint32_t tcap;
+    unsigned long long capV, capSG, capE;
+};
+
 // Vertices that a batched network of this prediction gets room for. The
 // prediction is rough for small networks (up to four times too low for D >= 5),
-// and a network that does not fit is extracted a second time: more room there
-// than a quarter on top.
-size_t vertex_room(double pred) {
-    return std::max<size_t>((size_t)(pred * 1.25) + 64, std::min<size_t>((size_t)(pred * 4.0) + 512, 8192));
+// and a network that does not fit is extracted a second time: with `spare`, more
+// room there than a quarter on top.
+size_t vertex_room(double pred, bool spare) {
+    const size_t least = (size_t)(pred * 1.25) + 64;
+    return spare ? std::max(least, std::min<size_t>((size_t)(pred * 4.0) + 512, 8192)) : least;
+}
+
+// idx: the batched networks among those of Ds, Wds and pred
+BatchRoom batch_room(const std::vector<int> &Ds, const std::vector<int> &Wds, const std::vector<double> &pred,
+                     const std::vector<int> &idx, int maxD, int maxWd, int maxZS, bool spare) {
+    BatchRoom r{};
+    size_t vcap = 0;
+    for (int i : idx) vcap = std::max(vcap, vertex_room(pred[i], spare));
+    r.vbytes = (vcap * 8 * (size_t)(maxD + maxWd + maxZS) + 255) / 256 * 256;
+    const int P = std::max(1, 2 * (maxD - 1));
+    r.ecap = (int)((vcap * (maxD + 1) + 15) / 16 * 16);
+    r.kcap = (int)std::max<size_t>(1024, (size_t)P * std::max<size_t>(256, vcap / 12));
+    r.tcap = 256;
+    while ((uint64_t)r.tcap < 2ull * (uint64_t)r.kcap && r.tcap < (1u << 31)) r.tcap <<= 1;
+    r.abytes = (batch_arena_bytes(r.vbytes, r.ecap, r.kcap, r.tcap) + 255) / 256 * 256;
+    double sv = 0, ssg = 0, se = 0;
+    for (int i : idx) {
+        const double v = std::min(spare ? (double)vertex_room(pred[i], true) : 1.1 * pred[i], (double)vcap);
+        sv += v * Ds[i];
+        ssg += v * Wds[i];
+        se += v * (Ds[i] + 1);
+    }
+    r.capV = (unsigned long long)sv + 1024;
+    r.capSG = (unsigned long long)ssg + 1024;
+    r.capE = (unsigned long long)se + 1024;
+    return r;
 }
 
 size_t align16(size_t x) { return (x + 15) / 16 * 16; }
@@ -134,7 +170,6 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
     std::vector<int> batched, direct;
     size_t box_off = 0;
     int maxD = 1, maxWd = 1, maxZS = 1;
-    double predV = 0;
     bool narrow = true;  // every batched network has layers of at most kSmallWidth neurons
     for (int i = 0; i < n; ++i) {
         const pcx_mlp *m = mlps[i];
@@ -196,7 +231,6 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
             maxWd = std::max(maxWd, Wd);
             maxZS = std::max(maxZS, ZS);
             narrow = narrow && ZS <= kSmallWidth && D <= 8;
-            predV = std::max(predV, pred[i]);
         } else {
             direct.push_back(i);
         }
@@ -219,17 +253,6 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
         int dev = 0, cus = 256;
         (void)hipGetDevice(&dev);
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        // per-workgroup arena from the largest batched network
-        const int P = 2 * (maxD - 1) > 0 ? 2 * (maxD - 1) : 1;
-        size_t vcap = vertex_room(predV);
-        size_t vbytes = vcap * 8 * (size_t)(maxD + maxWd + maxZS);
-        vbytes = (vbytes + 255) / 256 * 256;
-        int ecap = (int)(((size_t)vcap * (maxD + 1) + 15) / 16 * 16);
-        int kcap = (int)std::max<size_t>(1024, (size_t)P * std::max<size_t>(256, vcap / 12));
-        uint32_t tcap = 256;
-        while ((uint64_t)tcap < 2ull * (uint64_t)kcap && tcap < (1u << 31)) tcap <<= 1;
-        size_t abytes = batch_arena_bytes(vbytes, ecap, kcap, tcap);
-        abytes = (abytes + 255) / 256 * 256;
         // workgroups per CU and schedule: from the autotuner's cache, else 2 and the default
         const std::vector<int> sig = signature(bt->nsteps, bt->D, batched);
         bt->sig = sig;
@@ -254,39 +277,11 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
         // narrow networks under the default schedule: the small-network kernel
         const bool small = narrow && sched == kSchedDefault;
         if (small) grid = std::min(grid, cus);
-        // output pool from the predictions (overflowing networks fall back)
-        double sv = 0, ssg = 0, se = 0;
-        for (int i : batched) {
-            const double v = std::min((double)vertex_room(pred[i]), (double)vcap);
-            sv += v * bt->D[i];
-            ssg += v * bt->Wd[i];
-            se += v * (bt->D[i] + 1);
-        }
-        const unsigned long long capV = (unsigned long long)sv + 1024, capSG = (unsigned long long)ssg + 1024,
-                                 capE = (unsigned long long)se + 1024;
-        void *p;
         BatchArgs A{};
-        if ((rc = ar.alloc(&p, (size_t)grid * abytes))) goto fail_out;
-        A.arena = (char *)p;
-        if ((rc = ar.alloc(&p, capV * sizeof(double)))) goto fail_out;
-        bt->oX = (double *)p;
-        ar.forget(p);  // owned by the batch from here on
-        if ((rc = ar.alloc(&p, capSG * sizeof(uint64_t)))) goto fail_out;
-        bt->oSG = (uint64_t *)p;
-        ar.forget(p);  // owned by the batch from here on
-        if ((rc = ar.alloc(&p, capE * sizeof(int2)))) goto fail_out;
-        bt->oE = (int2 *)p;
-        ar.forget(p);  // owned by the batch from here on
         // the inputs in one block (the pool counters, zero; the order; the network
         // descriptors) and the outputs in one block (the results, and the step
         // log with kStepsNow), each moved by one copy through pinned memory
         in_bytes = 8 * sizeof(unsigned long long) + align16(batched.size() * sizeof(int)) + (size_t)n * sizeof(BatchNet);
-        if ((rc = ar.alloc(&p, in_bytes))) goto fail_out;
-        in_dev = (char *)p;
-        A.pool = (unsigned long long *)in_dev;
-        A.ticket = (int *)(A.pool + 4);
-        A.order = (const int *)(in_dev + 8 * sizeof(unsigned long long));
-        A.nets = (const BatchNet *)(in_dev + 8 * sizeof(unsigned long long) + align16(batched.size() * sizeof(int)));
         res_bytes = align16((size_t)n * sizeof(BatchResult));
         {
             size_t tot = 0;
@@ -294,8 +289,41 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
                 for (int i : batched) tot += (size_t)bt->nsteps[i];
             out_bytes = res_bytes + (steps_mode == kStepsNow ? std::max<size_t>(tot, 1) * sizeof(StepRec) : 0);
         }
-        if ((rc = ar.alloc(&p, out_bytes))) goto fail_out;
-        out_dev = (char *)p;
+        // Room for the networks' complexes: with spare if that can be had, else
+        // (a byte cap, or no memory) a quarter above the predictions, and the
+        // networks that outgrow it fall back to the per-step path.
+        BatchRoom room;
+        {
+            for (const bool spare : {true, false}) {
+                room = batch_room(bt->D, bt->Wd, pred, batched, maxD, maxWd, maxZS, spare);
+                void *q[6] = {};
+                const size_t bytes[6] = {(size_t)grid * room.abytes, room.capV * sizeof(double),
+                                         room.capSG * sizeof(uint64_t), room.capE * sizeof(int2),
+                                         in_bytes, out_bytes};
+                size_t total = 0;
+                for (size_t x : bytes) total += Pool::size_class(std::max<size_t>(x, 1));
+                if (spare && o.max_bytes && total > o.max_bytes) continue;
+                rc = PCX_OK;
+                for (int k = 0; k < 6 && !rc; ++k) rc = ar.alloc(&q[k], bytes[k]);
+                if (rc) {
+                    for (void *x : q) ar.release(x);
+                    continue;
+                }
+                A.arena = (char *)q[0];
+                bt->oX = (double *)q[1];
+                bt->oSG = (uint64_t *)q[2];
+                bt->oE = (int2 *)q[3];
+                in_dev = (char *)q[4];
+                out_dev = (char *)q[5];
+                for (int k = 1; k <= 3; ++k) ar.forget(q[k]);  // owned by the batch from here on
+                break;
+            }
+            if (rc) goto fail_out;
+        }
+        A.pool = (unsigned long long *)in_dev;
+        A.ticket = (int *)(A.pool + 4);
+        A.order = (const int *)(in_dev + 8 * sizeof(unsigned long long));
+        A.nets = (const BatchNet *)(in_dev + 8 * sizeof(unsigned long long) + align16(batched.size() * sizeof(int)));
         A.res = (BatchResult *)out_dev;
         if (keep_steps) {
             size_t tot = 0;
@@ -322,17 +350,17 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
             if (steps_mode == kStepsLater) bt->rec_off = rec_off;
         }
         A.n = (int)batched.size();
-        A.arena_bytes = abytes;
-        A.vbytes = vbytes;
-        A.ecap = ecap;
-        A.kcap = kcap;
-        A.tcap = tcap;
+        A.arena_bytes = room.abytes;
+        A.vbytes = room.vbytes;
+        A.ecap = room.ecap;
+        A.kcap = room.kcap;
+        A.tcap = room.tcap;
         A.oX = bt->oX;
         A.oSG = bt->oSG;
         A.oE = bt->oE;
-        A.capV = capV;
-        A.capSG = capSG;
-        A.capE = capE;
+        A.capV = room.capV;
+        A.capSG = room.capSG;
+        A.capE = room.capE;
         {
             // (PCX_DEBUG_HASH_BITS: as in pcx_extract, collisions on purpose for tests)
             const char *v = getenv("PCX_DEBUG_HASH_BITS");

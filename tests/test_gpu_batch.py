@@ -156,3 +156,40 @@ def test_batch_schedules_and_tuner(pcx, monkeypatch):
         for x, y in zip(bt.copy(i), ref[i]):
             assert np.array_equal(x, y)
     bt.close()
+
+
+@pytest.mark.parametrize("widths", [[2, 20, 20, 1], [3, 12, 8, 1], [2, 40, 70, 1]])
+def test_byte_cap_that_fits_a_quarter_above_the_predictions(pcx, widths):
+    """max_bytes of exactly what a batch takes with a quarter of room above its predictions: it is accepted (the spare
+    room that an uncapped batch takes is left out) and gives the complexes of the uncapped one."""
+    import math
+    n, D = 48, widths[0]
+    hidden = widths[1:-1]
+    N, ZS, Wd = sum(hidden), max(hidden), 1 + sum(-(-w // 32) for w in hidden)
+    pred = 0.6 * N ** D / math.prod(2.0 * k for k in range(2, D)) + 2.0 ** D + 4.0 * N
+    vcap, P = int(pred * 1.25) + 64, 2 * (D - 1)
+    ecap = (vcap * (D + 1) + 15) // 16 * 16
+    kcap = max(1024, P * max(256, vcap // 12))
+    tcap = 256
+    while tcap < 2 * kcap:
+        tcap *= 2
+    arena = vcap * 8 * (D + Wd + ZS) + 256 + ecap * 32 + kcap * 12 + 256 + tcap * 8 + 64 * 8 + 512
+    v = 1.1 * n * pred
+    blocks = [n * arena, (v * D + 1024) * 8, (v * Wd + 1024) * 8, (v * (D + 1) + 1024) * 8]
+    cap = sum((int(b) + (1 << 20)) >> 20 << 20 for b in blocks) + (128 << 10)  # blocks of whole MiB; descriptors, results
+    nets = [wl.he_mlp(widths, [210, i]) for i in range(n)]
+    mlps = [pcx.MLP.from_net(x) for x in nets]
+    boxes = [(wl.cube(D).lo, wl.cube(D).hi)] * n
+    pcx.cache_trim()  # (a larger block kept from before would count against the cap)
+    capped = pcx.Batch(mlps, boxes, max_bytes=cap)
+    free = pcx.Batch(mlps, boxes)
+    for i in range(n):
+        for a, b in zip(capped.copy(i), free.copy(i)):
+            assert a.shape == b.shape and np.array_equal(a, b), f"network {i}"
+    capped.close()
+    free.close()
+    with pytest.raises(pcx.PcxError) as e:
+        pcx.Batch(mlps, boxes, max_bytes=1 << 20)
+    assert e.value.code == pcx.PCX_ERR_CAPACITY
+    for m in mlps:
+        m.close()
