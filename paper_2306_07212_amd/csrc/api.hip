@@ -527,7 +527,7 @@ bool tiny_eligible(const pcx_mlp *mlp, const pcx_opts &o, int nsub) {
     const char *off = getenv("PCX_NO_TINY");
     if (off && off[0] == '1') return false;
     if (o.pairing != PCX_PAIR_HASH || o.prune || o.record_tape || o.timing || o.max_bytes) return false;
-    if (mlp->D > kBatchMaxD || mlp->L > kBatchMaxLayers) return false;
+    if (mlp->D > kBatchMaxD || mlp->L > kBatchMaxLayers || mlp->outgrew.load()) return false;
     int N = 0, Wd = 1, widest = 0;
     for (int l = 1; l <= nsub; ++l) {
         if (mlp->widths[l] > kMaxWidth) return false;

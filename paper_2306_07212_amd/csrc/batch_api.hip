@@ -21,6 +21,7 @@ struct pcx_batch {
     int2 *oE = nullptr;
     double time_ms = 0.0, kernel_ms = 0.0;
     int workgroups = 0, wg_per_cu = 0, n_fallback = 0;
+    bool outgrown = false;                    // a network did not fit its room
     int sched = 0;                            // schedule bits of the launch (kSched*)
     std::vector<int> sig;                     // size signature of the batched networks
     std::vector<std::vector<int64_t>> steps;  // per-step counters of each batched network (kStepsNow)
@@ -96,31 +97,50 @@ struct BatchRoom {
     unsigned long long capV, capSG, capE;
 };
 
-// Vertices that a batched network of this prediction gets room for. The
-// prediction is rough for small networks (up to four times too low for D >= 5),
-// and a network that does not fit is extracted a second time: with `spare`, more
-// room there than a quarter on top.
-size_t vertex_room(double pred, bool spare) {
-    const size_t least = (size_t)(pred * 1.25) + 64;
-    return spare ? std::max(least, std::min<size_t>((size_t)(pred * 4.0) + 512, 8192)) : least;
+// Vertices and key slots that a batched network gets room for. The least is a
+// quarter above the prediction, and key slots for steps of a twelfth of that. The
+// prediction falls short from D = 4 on and the last steps of a network of few
+// neurons split more of it, and a network that does not fit is extracted a second
+// time, so with `spare` both are sized by D. Largest over 2,554 He networks of 1 to
+// 4 layers (V above 512 over the prediction; S, the largest step, over V):
+//   D = 3: 0.9, 0.17;  4: 1.6, 0.26;  5: 4.4, 0.32;  6: 14, 0.35;  8: 76, 0.44.
+// (Every workgroup clears its key slots for every network: no more spare of them
+// than 24K or twice the least.)
+size_t least_vertices(double pred) { return (size_t)(pred * 1.25) + 64; }
+size_t vertex_room(int D, double pred, bool spare) {
+    const size_t least = least_vertices(pred);
+    if (!spare) return least;
+    const double grown = pred * (D <= 3 ? 1.25 : std::pow(2.5, D - 3)) + 512.0;
+    return D <= 3 ? (size_t)grown : std::max<size_t>(least, (size_t)std::min(grown, 12288.0));
+}
+size_t key_room(int D, double pred, bool spare) {
+    const size_t P = std::max(1, 2 * (D - 1));
+    const size_t least = P * std::max<size_t>(256, least_vertices(pred) / 12);
+    if (!spare || D <= 2) return least;
+    const size_t grown = P * std::max<size_t>(256, vertex_room(D, pred, true) * D / 14);
+    return std::max(least, std::min(grown, std::max<size_t>(24576, 2 * least)));
 }
 
 // idx: the batched networks among those of Ds, Wds and pred
 BatchRoom batch_room(const std::vector<int> &Ds, const std::vector<int> &Wds, const std::vector<double> &pred,
                      const std::vector<int> &idx, int maxD, int maxWd, int maxZS, bool spare) {
     BatchRoom r{};
-    size_t vcap = 0;
-    for (int i : idx) vcap = std::max(vcap, vertex_room(pred[i], spare));
+    size_t vcap = 0, kcap = 1024;
+    double largest = 0;
+    for (int i : idx) {
+        vcap = std::max(vcap, vertex_room(Ds[i], pred[i], spare));
+        kcap = std::max(kcap, key_room(Ds[i], pred[i], spare));
+        largest = std::max(largest, pred[i]);
+    }
     r.vbytes = (vcap * 8 * (size_t)(maxD + maxWd + maxZS) + 255) / 256 * 256;
-    const int P = std::max(1, 2 * (maxD - 1));
     r.ecap = (int)((vcap * (maxD + 1) + 15) / 16 * 16);
-    r.kcap = (int)std::max<size_t>(1024, (size_t)P * std::max<size_t>(256, vcap / 12));
+    r.kcap = (int)std::max(kcap, key_room(maxD, largest, false));
     r.tcap = 256;
     while ((uint64_t)r.tcap < 2ull * (uint64_t)r.kcap && r.tcap < (1u << 31)) r.tcap <<= 1;
     r.abytes = (batch_arena_bytes(r.vbytes, r.ecap, r.kcap, r.tcap) + 255) / 256 * 256;
     double sv = 0, ssg = 0, se = 0;
     for (int i : idx) {
-        const double v = std::min(spare ? (double)vertex_room(pred[i], true) : 1.1 * pred[i], (double)vcap);
+        const double v = std::min(spare ? (double)vertex_room(Ds[i], pred[i], true) : 1.1 * pred[i], (double)vcap);
         sv += v * Ds[i];
         ssg += v * Wds[i];
         se += v * (Ds[i] + 1);
@@ -407,6 +427,7 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
         bt->wg_per_cu = wpc;
         for (int i : batched) {
             const int s = bt->res[i].status;
+            if (s == BATCH_OVERFLOW || s == BATCH_POOL) bt->outgrown = true;
             if (s == BATCH_OVERFLOW || s == BATCH_POOL || s == BATCH_RETRY) direct.push_back(i);
             else if (s == BATCH_INTERNAL) {
                 rc = fail(PCX_ERR_DEVICE, "internal error in the batched kernel");
@@ -479,7 +500,8 @@ int tiny_extract(const pcx_mlp *mlp, const double *lo, const double *hi, const p
         pcx_batch_free(bt);
         return fail(PCX_ERR_DEGENERATE, "input is not generic");
     }
-    if (bt->fallback[0]) {  // too large for the kernel's arena: the per-step path ran
+    if (bt->fallback[0]) {  // too large for the kernel's arena: the per-step path ran, and will at once from now on
+        if (bt->outgrown) const_cast<pcx_mlp *>(mlp)->outgrew.store(true);
         *out = bt->fallback[0];
         bt->fallback[0] = nullptr;
         pcx_batch_free(bt);

@@ -57,6 +57,7 @@ struct pcx_mlp {
     std::vector<double *> b;   // device, [N_l]
     std::vector<char> finite;  // layer l: every weight is finite (0 * w = 0)
     std::atomic<int64_t> hintV{0}, hintE{0}, hintS{0};  // sizes seen by earlier extractions (capacity hints)
+    std::atomic<bool> outgrew{false};  // a batch of one did not hold its complex: its extractions go per step
     pcx::GraphCache *gcache = nullptr;  // the last extraction's step log and its captured graph (graph.hip)
 };
 
