@@ -268,8 +268,9 @@ def form_batched(args, pcx, wl, torch):
     achieved = b8 / k_med / 1e9
     roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "bytes_per_launch": b8,
-            # (layers of up to 64 neurons: the small-network kernel under the default schedule)
-            "kernel": "pcx::k_small" if (tuned["split_lanes"], tuned["select_items"]) == (16, 16) else "pcx::k_batch",
+            # (layers of up to 64 neurons: the small-network kernel is the default schedule at one workgroup a CU)
+            "kernel": "pcx::k_small" if (tuned["wg_per_cu"], tuned["split_lanes"], tuned["select_items"]) == (1, 16, 16)
+            else "pcx::k_batch",
             "launches_per_step": 1, "avg_launch_us": k_med * 1e6, "traffic": None,
             "bytes_rule": "scope-table count summed over every network's steps; the launch also evaluates "
                           "every layer (FP64 MFMA for layers of up to 64 neurons, not in the count)"}

@@ -65,7 +65,8 @@ typedef struct {
                                pre-activations); costs V * N_l doubles per subdivided layer */
     uint64_t max_bytes;     /* cap on device bytes the extraction may hold; 0 = no cap */
     void *stream;           /* hipStream_t to run on; NULL = the default stream */
-    int32_t batch_wg_per_cu;/* pcx_extract_batch: workgroups per compute unit; 0 = tuned / default */
+    int32_t batch_wg_per_cu;/* pcx_extract_batch: workgroups per compute unit; 0 = tuned, else 2 (1 where every
+                               network's layers have at most 64 neurons) */
     int32_t prune;          /* 1 (needs include_output; pcx_extract only, not with record_tape): pruning
                                during subdivision for level-set extraction (Sec. 5.4.2). Before each
                                subdivided layer, edges whose two vertices agree in sign on every neuron
@@ -202,9 +203,9 @@ int pcx_complex_kernel_time(const pcx_complex *cx, int32_t family, double *ms, i
 void pcx_complex_free(pcx_complex *cx);
 
 /* ---- Batched extraction: many networks in one persistent launch ----------
- * (Under the default schedule a batch of networks with layers of at most 64
- * neurons runs by larger workgroups, one a compute unit whatever
- * batch_wg_per_cu.) Each network is extracted exactly as pcx_extract would (same vertex and edge
+ * (A batch of networks with layers of at most 64 neurons runs by larger
+ * workgroups, one a compute unit, under the default schedule, unless
+ * batch_wg_per_cu asks for two or more.) Each network is extracted exactly as pcx_extract would (same vertex and edge
  * numbering, bit-identical values); a workgroup runs one network at a time
  * from a largest-first queue. Networks that exceed the batched kernel's limits
  * (D > 8, more than 8 layers, a layer wider than 256, or a predicted complex
@@ -238,16 +239,18 @@ int pcx_batch_summary(const pcx_batch *bt, pcx_batch_stats *stats);
 void pcx_batch_free(pcx_batch *bt);
 /* Autotuner: times the batch's persistent launch under each of six schedules
  * (lanes per splitting edge 16, 32 or 64; edges per thread in each step's
- * compaction 16 or 8) at 2 workgroups per compute unit, then 1 and 4 workgroups per compute
- * unit under the best schedule (best of two launches each), and keeps the
+ * compaction 16 or 8), the default one as an untuned batch runs it and the others
+ * at 2 workgroups per compute unit, then the best schedule at the other two of 1, 2
+ * and 4 workgroups per compute unit (best of two launches each), and keeps the
  * fastest for batches with the same size signature (the sorted subdivided-
- * neuron counts and input dimensions of the batched networks); later
+ * neuron counts and input dimensions of the batched networks, and whether all their
+ * layers have at most 64 neurons); later
  * pcx_extract_batch calls of that signature use it (batch_wg_per_cu > 0 still
  * overrides the occupancy). result (may be NULL) receives the choice. */
 typedef struct {
     int32_t wg_per_cu, split_lanes, select_items;
     int32_t candidates;     /* launches configurations timed */
-    double ms_default;      /* kernel time with the default schedule: 2 per CU, 16 lanes, 16 edges */
+    double ms_default;      /* kernel time as an untuned batch runs: 16 lanes, 16 edges, 2 per CU (or 1, as above) */
     double ms_best;         /* kernel time with the chosen one */
 } pcx_batch_tuning;
 int pcx_batch_tune(int32_t n, const pcx_mlp *const *mlps, const double *lo, const double *hi,

@@ -250,7 +250,7 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
             maxD = std::max(maxD, D);
             maxWd = std::max(maxWd, Wd);
             maxZS = std::max(maxZS, ZS);
-            narrow = narrow && ZS <= kSmallWidth && D <= 8;
+            narrow = narrow && ZS <= kSmallWidth;
         } else {
             direct.push_back(i);
         }
@@ -273,30 +273,34 @@ int batch_run(int32_t n, const pcx_mlp *const *mlps, const double *lo, const dou
         int dev = 0, cus = 256;
         (void)hipGetDevice(&dev);
         (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        // workgroups per CU and schedule: from the autotuner's cache, else 2 and the default
-        const std::vector<int> sig = signature(bt->nsteps, bt->D, batched);
-        bt->sig = sig;
-        int wpc = 2, sched = kSchedDefault;
-        {
+        // schedule and workgroups per CU: as asked, else from the autotuner's cache,
+        // else the default ones. Narrow networks under the default schedule run on the
+        // small-network kernel where one workgroup a CU is asked for or nothing is;
+        // two and more are the 256-thread kernel's.
+        bt->sig = signature(bt->nsteps, bt->D, batched);
+        bt->sig.push_back(narrow);
+        int wpc = 0, sched = force_sched;
+        bool hook = false;
+        if (sched < 0) {
+            // test hook: one schedule of the 256-thread kernel for every launch (0 .. kSchedCount-1)
+            const char *v = getenv("PCX_BATCH_SCHED");
+            hook = v && *v;
+            if (hook) sched = std::max(0, std::min(kSchedCount - 1, atoi(v)));
+        }
+        if (sched < 0) {
             std::lock_guard<std::mutex> lk(g_tune_mu);
-            auto it = g_tuned.find(sig);
+            auto it = g_tuned.find(bt->sig);
             if (it != g_tuned.end()) {
                 wpc = it->second.first;
                 sched = it->second.second;
             }
         }
+        if (sched < 0) sched = kSchedDefault;
         if (o.batch_wg_per_cu > 0) wpc = o.batch_wg_per_cu;
-        if (force_sched < 0) {
-            // test hook: one schedule for every launch (0 .. kSchedCount-1)
-            const char *v = getenv("PCX_BATCH_SCHED");
-            if (v && *v) force_sched = std::max(0, std::min(kSchedCount - 1, atoi(v)));
-        }
-        if (force_sched >= 0) sched = force_sched;
+        if (wpc == 0) wpc = narrow && sched == kSchedDefault && !hook ? 1 : 2;
+        const bool small = narrow && sched == kSchedDefault && wpc == 1 && !hook;
         bt->sched = sched;
-        int grid = std::min<int>((int)batched.size(), cus * wpc);
-        // narrow networks under the default schedule: the small-network kernel
-        const bool small = narrow && sched == kSchedDefault;
-        if (small) grid = std::min(grid, cus);
+        const int grid = std::min<int>((int)batched.size(), cus * wpc);
         BatchArgs A{};
         // the inputs in one block (the pool counters, zero; the order; the network
         // descriptors) and the outputs in one block (the results, and the step
@@ -632,9 +636,11 @@ void pcx_batch_free(pcx_batch *bt) {
 
 int pcx_batch_tune(int32_t n, const pcx_mlp *const *mlps, const double *lo, const double *hi, const pcx_opts *opts,
                    pcx_batch_tuning *result) {
-    // time the batch's launch under each schedule at two workgroups per CU,
-    // then each occupancy under the best schedule (best of two launches each)
+    // time the batch's launch under the default schedule as an untuned batch runs
+    // it, under each other one at two workgroups per CU, then the other occupancies
+    // of 1, 2 and 4 under the best schedule (best of two launches each)
     std::vector<int> sig;
+    int ran_wpc = 2;
     auto measure = [&](int wpc, int sched, double *ms) -> int {
         *ms = 1e300;
         for (int rep = 0; rep < 2; ++rep) {
@@ -646,6 +652,7 @@ int pcx_batch_tune(int32_t n, const pcx_mlp *const *mlps, const double *lo, cons
             if (rc) return rc;
             *ms = std::min(*ms, bt->kernel_ms);
             sig = bt->sig;
+            if (bt->wg_per_cu) ran_wpc = bt->wg_per_cu;  // (0: no network was batched)
             pcx_batch_free(bt);
         }
         return PCX_OK;
@@ -655,15 +662,18 @@ int pcx_batch_tune(int32_t n, const pcx_mlp *const *mlps, const double *lo, cons
     for (int i = 0; i < kSchedCount; ++i) {
         // the default first, then the others in order
         const int sc = i == 0 ? kSchedDefault : (i <= kSchedDefault ? i - 1 : i);
-        if ((rc = measure(2, sc, &ms))) return rc;
+        if ((rc = measure(i == 0 ? 0 : 2, sc, &ms))) return rc;
         ++tried;
         if (i == 0) ms_default = ms;
         if (ms < best) {
             best = ms;
             best_sched = sc;
+            best_wpc = ran_wpc;
         }
     }
-    for (int w : {1, 4}) {
+    const int timed_wpc = best_wpc;
+    for (int w : {1, 2, 4}) {
+        if (w == timed_wpc) continue;
         if ((rc = measure(w, best_sched, &ms))) return rc;
         ++tried;
         if (ms < best) {

@@ -193,3 +193,38 @@ def test_byte_cap_that_fits_a_quarter_above_the_predictions(pcx, widths):
     assert e.value.code == pcx.PCX_ERR_CAPACITY
     for m in mlps:
         m.close()
+
+
+def test_occupancy_asked_for_is_the_occupancy_run(pcx, monkeypatch):
+    """wg_per_cu of a batch of narrow networks (the small-network kernel's, one workgroup a CU, unless more are asked
+    for) and of one that holds a wider layer, with more networks than workgroups: the launch and the stats follow."""
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 4 * cus + 8
+    box = (wl.cube(2).lo, wl.cube(2).hi)
+    narrow = [pcx.MLP.from_net(wl.he_mlp([2, 3 + i % 3, 2, 1], [211, i])) for i in range(n)]
+    mixed = narrow[:-1] + [pcx.MLP.from_net(wl.he_mlp([2, 65, 1], 212))]
+    ref = None
+    for mlps, default in ((narrow, 1), (mixed, 2)):
+        for asked in (0, 1, 2, 4):
+            bt = pcx.Batch(mlps, [box] * n, wg_per_cu=asked)
+            st = bt.stats()
+            want = asked or default
+            assert (st.wg_per_cu, st.workgroups) == (want, want * cus), (asked, default)
+            got = [bt.copy(i) for i in range(0, n - 1, 37)]
+            bt.close()
+            ref = ref or got
+            for a, b in zip(got, ref):
+                for x, y in zip(a, b):
+                    assert np.array_equal(x, y), (asked, default)
+    t = pcx.batch_tune(narrow, [box] * n)
+    print(f"tuned: {t}", flush=True)
+    bt = pcx.Batch(narrow, [box] * n)
+    st = bt.stats()
+    assert (st.wg_per_cu, st.split_lanes, st.select_items) == (t["wg_per_cu"], t["split_lanes"], t["select_items"])
+    bt.close()
+    bt = pcx.Batch(mixed, [box] * n)  # (the same neuron counts but for one network; untuned)
+    assert bt.stats().wg_per_cu == 2
+    bt.close()
+    for m in narrow + mixed[-1:]:
+        m.close()
