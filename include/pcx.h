@@ -130,7 +130,8 @@ void pcx_mlp_free(pcx_mlp *mlp);
  * 120 for D = 4, 5 and 6) runs as a batch of one instead (one launch, the same
  * complex; PCX_NO_TINY=1 turns this off, PCX_TINY_VERTICES sets the threshold
  * for every D); so does one with wider layers on the line (15000), or in the
- * plane behind a first layer of at most 10 neurons (10000). */
+ * plane where few vertices arise for its steps, as behind narrow layers (10000).
+ * A network whose complex does not fit there goes per step from then on. */
 int pcx_extract(const pcx_mlp *mlp, const double *lo, const double *hi, const pcx_opts *opts,
                 pcx_complex **out);
 

@@ -511,17 +511,28 @@ struct Domain {
 //   D = 3:  2,717: 0.46, 0.62 / 0.48; 4,822: 0.74, 0.74 / 0.52
 //   D = 4:  1,250: 0.25, 0.40 / 0.28; 2,593: 0.44, 0.48 / 0.34
 //   D = 5:  1,047: 0.21, 0.33 / 0.22; D = 6: 789: 0.17, 0.29 / 0.18
-// Networks with a wider layer take the batched kernel's 256-thread workgroup where
-// few vertices arise for their steps, which cost it 5 us each and the per-step
-// kernels 11 / 9: on the line (1-204-204: 2.33 ms against 5.07 / 4.04), and in the
-// plane behind a first layer of few neurons (2-5-5-100, 1,378 vertices: 1.05, 1.55 /
-// 1.22; but 2-16-70, 2,289: 1.24, 1.31 / 1.07; 2-100-30, 5,960: 2.86, 2.09 / 1.74).
+// Networks with a wider layer take the batched kernel's 256-thread workgroup on the
+// line (1-204-204: 2.33 ms against 5.07 / 4.04), and in the plane where few vertices
+// arise for their steps: a step costs it 5 us and more with every split, and the
+// per-step kernels 11 to 15 whatever it splits. Over 60 networks the two meet near 24
+// vertices a step on first extractions and 17 on replays. A layer of N neurons has
+// 0.39 N a step, fewer behind narrow ones (0.2 + 0.055 w of that for a layer of
+// w < 15 neurons before the last); ms on a first extraction, one workgroup / per step:
+//   2-4-100: 1.10 / 1.40; 2-10-65: 1.05 / 1.13; 2-30-2-90: 1.42 / 1.67;
+//   2-8-8-8-100: 1.44 / 1.68; but 2-10-100: 2.04 / 1.63; 2-16-65: 1.31 / 1.24;
+//   2-100-30: 3.03 / 1.98; 2-65: 1.02 both (0.99 / 0.87 on replays).
 double tiny_vertices(int D) {
     static const double limit[7] = {0.0, 15000.0, 15000.0, 4200.0, 1800.0, 500.0, 120.0};
     return D <= 6 ? limit[D] : 0.0;
 }
-double tiny_wide_vertices(const pcx_mlp *mlp) {
-    return mlp->D == 1 ? 15000.0 : mlp->D == 2 && mlp->widths[1] <= 10 ? 10000.0 : 0.0;
+double tiny_wide_vertices(const pcx_mlp *mlp, int nsub) {
+    if (mlp->D != 2) return mlp->D == 1 ? 15000.0 : 0.0;
+    double per_step = 0.0, left = 0.39;
+    for (int l = 1; l <= nsub; ++l) {
+        per_step += mlp->widths[l];
+        if (l < nsub) left *= std::min(1.0, 0.2 + 0.055 * mlp->widths[l]);
+    }
+    return per_step * left < 24.0 ? 10000.0 : 0.0;
 }
 bool tiny_eligible(const pcx_mlp *mlp, const pcx_opts &o, int nsub) {
     const char *off = getenv("PCX_NO_TINY");
@@ -535,7 +546,7 @@ bool tiny_eligible(const pcx_mlp *mlp, const pcx_opts &o, int nsub) {
         N += mlp->widths[l];
         Wd += (mlp->widths[l] + 31) / 32;
     }
-    double limit = widest <= kSmallWidth ? tiny_vertices(mlp->D) : tiny_wide_vertices(mlp);
+    double limit = widest <= kSmallWidth ? tiny_vertices(mlp->D) : tiny_wide_vertices(mlp, nsub);
     if (const char *v = getenv("PCX_TINY_VERTICES")) limit = atof(v);
     return Wd <= kBatchMaxWords && N > 0 && predict_vertices(mlp->D, N) <= limit;
 }
