@@ -52,3 +52,16 @@ def test_every_form_of_the_split_list_gives_the_same_complex(oracle_lib, monkeyp
         X, SG, Ed, steps = ref
         assert np.array_equal(steps, r.steps)
         assert_same_complex((X, unpack_signs(SG, net.widths), Ed), (r.X, r.S, r.edges))
+
+
+@pytest.mark.parametrize("widths,batched", [(w, w != [3, 200, 1]) for w, _ in CASES])
+def test_which_of_the_networks_the_batched_kernel_serves(widths, batched):
+    """The batched form above is the one-workgroup kernels' own for every network but 3-200-1, whose prediction is
+    above what a batch takes: nothing else falls back to the per-step path."""
+    from paper_2306_07212_amd import pcx
+    m, box = pcx.MLP.from_net(wl.he_mlp(widths, [91, len(widths)])), wl.cube(widths[0])
+    bt = pcx.Batch([m], [(box.lo, box.hi)])
+    st = bt.stats()
+    assert st.fallbacks == (0 if batched else 1), st
+    bt.close()
+    m.close()
