@@ -244,6 +244,7 @@ __global__ __launch_bounds__(kThreads) void k_region_keys(const uint64_t *__rest
 // 448 rows, the whole call 0.33 ms instead of 0.50. The pairs grow with n^2: 9K
 // rows 0.46 ms instead of 0.50, 17K 0.69 instead of 0.55, so the line lies between.
 constexpr int64_t kRankRows = 8192;
+constexpr int64_t kPieceBytes = 16 << 20;  // of ordered rows per copy to the host
 __global__ __launch_bounds__(kThreads) void k_region_rank(const uint64_t *__restrict__ rows, int n, int Wd,
                                                           uint64_t *__restrict__ out) {
     const int i = (blockIdx.x * kThreads + threadIdx.x) >> 6, lane = threadIdx.x & 63;
@@ -395,14 +396,39 @@ int pcx_regions(const pcx_complex *cx, uint64_t *rows, int64_t *n, void *stream)
     uint64_t *drows = (uint64_t *)p;
     if ((rc = ar.alloc(&p, Wd * sizeof(uint64_t)))) return rc;
     uint64_t *valid = (uint64_t *)p;
+    if (D == 1) {
+        if ((rc = ar.alloc(&p, (size_t)nr * sizeof(int2)))) return rc;
+        reg = (int2 *)p;
+    }
+    // deterministic order: lexicographic by sign row (words from the first). The sort
+    // takes the cells' and their keys' storage, which the rows leave free, and the
+    // ordered rows go to the host in pieces, so that a call holds the rows once; all
+    // of it is allocated before the first launch.
+    const bool few = nr <= kRankRows;
+    const int64_t piece = few ? nr : std::min<int64_t>(nr, std::max<int64_t>(1, kPieceBytes / (Wd * 8)));
+    if ((rc = ar.alloc(&p, (size_t)piece * Wd * sizeof(uint64_t)))) return rc;
+    uint64_t *sorted = (uint64_t *)p;
+    Bufs sb{};
+    if (!few) {
+        if (!keys) {
+            if ((rc = ar.alloc(&p, (size_t)nr * sizeof(uint64_t)))) return rc;
+            keys = (unsigned long long *)p;
+        }
+        sb.K64a = reinterpret_cast<uint64_t *>(reg);
+        sb.K64b = reinterpret_cast<uint64_t *>(keys);
+        if ((rc = ar.alloc(&p, (size_t)nr * sizeof(uint32_t)))) return rc;
+        sb.VALa = (uint32_t *)p;
+        if ((rc = ar.alloc(&p, (size_t)nr * sizeof(uint32_t)))) return rc;
+        sb.VALb = (uint32_t *)p;
+        if ((rc = ar.alloc(&p, (size_t)kSortBins * ((nr + kSortTile - 1) / kSortTile + 1) * sizeof(uint32_t)))) return rc;
+        sb.HIST = (uint32_t *)p;
+    }
     HIPCHK(hipMemcpyAsync(valid, cx->valid.data(), Wd * sizeof(uint64_t), hipMemcpyHostToDevice, st));
     if (D == 1) {
         // the regions are the edges: their rows are the joins of their vertices
-        if ((rc = ar.alloc(&p, (size_t)nr * sizeof(int2)))) return rc;
         std::vector<int2> idc(nr);
         for (int64_t i = 0; i < nr; ++i) idc[i] = make_int2((int)i, 0);
-        HIPCHK(hipMemcpyAsync(p, idc.data(), nr * sizeof(int2), hipMemcpyHostToDevice, st));
-        reg = (int2 *)p;
+        HIPCHK(hipMemcpyAsync(reg, idc.data(), nr * sizeof(int2), hipMemcpyHostToDevice, st));
         HIPCHK(hipStreamSynchronize(st));
     }
     const int G = cell_lanes(D, Wd);
@@ -414,26 +440,12 @@ int pcx_regions(const pcx_complex *cx, uint64_t *rows, int64_t *n, void *stream)
     else if (G == 32) fill(k_cell_rows<32>);
     else fill(k_cell_rows<64>);
     HIPCHK(hipGetLastError());
-    // deterministic order: lexicographic by sign row (words from the first)
-    if ((rc = ar.alloc(&p, (size_t)nr * Wd * sizeof(uint64_t)))) return rc;
-    uint64_t *sorted = (uint64_t *)p;
-    if (nr <= kRankRows) {
+    const uint32_t *order = nullptr;
+    if (few) {
         hipLaunchKernelGGL(k_region_rank, dim3((unsigned)((nr + kThreads / 64 - 1) / (kThreads / 64))), dim3(kThreads), 0,
                            st, drows, (int)nr, Wd, sorted);
     } else {
-        Bufs sb{};
-        if ((rc = ar.alloc(&p, (size_t)nr * sizeof(uint64_t)))) return rc;
-        sb.K64a = (uint64_t *)p;
-        if ((rc = ar.alloc(&p, (size_t)nr * sizeof(uint64_t)))) return rc;
-        sb.K64b = (uint64_t *)p;
-        if ((rc = ar.alloc(&p, (size_t)nr * sizeof(uint32_t)))) return rc;
-        sb.VALa = (uint32_t *)p;
-        if ((rc = ar.alloc(&p, (size_t)nr * sizeof(uint32_t)))) return rc;
-        sb.VALb = (uint32_t *)p;
-        if ((rc = ar.alloc(&p, (size_t)kSortBins * ((nr + kSortTile - 1) / kSortTile + 1) * sizeof(uint32_t)))) return rc;
-        sb.HIST = (uint32_t *)p;
         const int grid = (int)std::min<int64_t>(8192, (nr + kThreads - 1) / kThreads);
-        const uint32_t *order = nullptr;
         for (int w = 1 + (Wd - 2) / 2 * 2; w >= 1; w -= 2) {
             hipLaunchKernelGGL(k_region_keys, dim3(grid), dim3(kThreads), 0, st, drows, (int)nr, Wd, w, order, sb.K64a);
             // the key's bytes in use: its low half is empty when the row ends with its first word
@@ -442,13 +454,17 @@ int pcx_regions(const pcx_complex *cx, uint64_t *rows, int64_t *n, void *stream)
             launch_sort64(sb, (int)nr, st, &sk, &order, first, 8 - first, order != nullptr);
             if (order == sb.VALb) std::swap(sb.VALa, sb.VALb);  // (the next sort reads the order so far)
         }
-        const int gg = (int)std::min<int64_t>(8192, (nr * Wd + kThreads - 1) / kThreads);
-        hipLaunchKernelGGL(k_region_gather, dim3(gg), dim3(kThreads), 0, st, drows, (int)nr, Wd, order, sorted);
     }
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(rows, sorted, (size_t)nr * Wd * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
+    for (int64_t i = 0; i < nr; i += piece) {
+        const int64_t m = std::min(piece, nr - i);
+        if (!few) {
+            const int gg = (int)std::min<int64_t>(8192, (m * Wd + kThreads - 1) / kThreads);
+            hipLaunchKernelGGL(k_region_gather, dim3(gg), dim3(kThreads), 0, st, drows, (int)m, Wd, order + i, sorted);
+        }
+        HIPCHK(hipGetLastError());
+        HIPCHK(hipMemcpyAsync(rows + i * Wd, sorted, (size_t)m * Wd * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
+    }
     HIPCHK(hipStreamSynchronize(st));
-    (void)keys;
     return PCX_OK;
 }
 
