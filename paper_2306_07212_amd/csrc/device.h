@@ -10,6 +10,8 @@
 
 namespace pcx {
 
+typedef double dbl4 __attribute__((ext_vector_type(4)));  // a lane's results of an FP64 16x16x4 MFMA
+
 // ---------------------------------------------------------------- helpers
 
 __device__ __forceinline__ uint64_t mix64(uint64_t x) {

@@ -19,8 +19,6 @@ namespace pcx {
 // adds a zero, which leaves any sum other than -0 unchanged, and a sum started
 // at +0 becomes -0 only if a product underflows), and then + bias: the values
 // are those of every other evaluation kernel, bit for bit.
-typedef double dbl4 __attribute__((ext_vector_type(4)));
-
 // (Not inlined, and given plain pointers rather than the workgroup's Bufs, so
 // that its registers and the Bufs stay out of the split's register allocation.)
 // (The pointers are taken as global memory, so that the loads are global
@@ -33,11 +31,11 @@ typedef __attribute__((address_space(1))) double gdouble;
 typedef __attribute__((address_space(1))) uint64_t guint64;
 
 template <int CT, int T = kThreads>
-__device__ __noinline__ void eval_mfma(double *Zo_, uint64_t *SGo_, uint64_t *LWo_, int *ctr, int ZS,
+__device__ __noinline__ void eval_mfma(double *Zo_, uint64_t *SGo_, int *ctr, int ZS,
                                        const double *in_, int in_stride, int relu, int V, int K, int N,
                                        const double *Wt_, const double *bias_, int Wd, int lw0) {
     gdouble *Zo = (gdouble *)Zo_;
-    guint64 *SGo = (guint64 *)SGo_, *LWo = (guint64 *)LWo_;
+    guint64 *SGo = (guint64 *)SGo_;
     gcuint64 *in = (gcuint64 *)in_, *Wt = (gcuint64 *)Wt_;
     gcdouble *bias = (gcdouble *)bias_;
     const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -117,9 +115,7 @@ __device__ __noinline__ void eval_mfma(double *Zo_, uint64_t *SGo_, uint64_t *LW
                         pos |= (uint32_t)((pb[2 * p + 1] >> sh) & 0xFFFFu) << 16;
                         neg |= (uint32_t)((nb[2 * p + 1] >> sh) & 0xFFFFu) << 16;
                     }
-                    const uint64_t cw = codes_of(pos, neg);
-                    SGo[(size_t)v * Wd + lw0 + p] = cw;
-                    if (LWo) LWo[(size_t)v * 8 + p] = cw;
+                    SGo[(size_t)v * Wd + lw0 + p] = codes_of(pos, neg);
                 }
             }
         }
@@ -131,10 +127,10 @@ __device__ __noinline__ void eval_mfma(double *Zo_, uint64_t *SGo_, uint64_t *LW
 template <int T>
 __device__ __forceinline__ void eval_strips(const Bufs &b, int ZS, const double *in, int ins, int relu, int V, int K,
                                             int N, const double *Wt, const double *bias, int Wd, int lw0) {
-    if (N <= 16) eval_mfma<1, T>(b.Z, b.SG, b.LW, b.CTR, ZS, in, ins, relu, V, K, N, Wt, bias, Wd, lw0);
-    else if (N <= 32) eval_mfma<2, T>(b.Z, b.SG, b.LW, b.CTR, ZS, in, ins, relu, V, K, N, Wt, bias, Wd, lw0);
-    else if (N <= 48) eval_mfma<3, T>(b.Z, b.SG, b.LW, b.CTR, ZS, in, ins, relu, V, K, N, Wt, bias, Wd, lw0);
-    else eval_mfma<4, T>(b.Z, b.SG, b.LW, b.CTR, ZS, in, ins, relu, V, K, N, Wt, bias, Wd, lw0);
+    if (N <= 16) eval_mfma<1, T>(b.Z, b.SG, b.CTR, ZS, in, ins, relu, V, K, N, Wt, bias, Wd, lw0);
+    else if (N <= 32) eval_mfma<2, T>(b.Z, b.SG, b.CTR, ZS, in, ins, relu, V, K, N, Wt, bias, Wd, lw0);
+    else if (N <= 48) eval_mfma<3, T>(b.Z, b.SG, b.CTR, ZS, in, ins, relu, V, K, N, Wt, bias, Wd, lw0);
+    else eval_mfma<4, T>(b.Z, b.SG, b.CTR, ZS, in, ins, relu, V, K, N, Wt, bias, Wd, lw0);
 }
 
 }  // namespace pcx

@@ -1,9 +1,12 @@
 // Device kernels of libpcx.so: edge subdivision (Berzins 2023, Sec. 4.2) on
-// gfx950. One neuron step is: compaction of the splitting edges (step 3),
-// interpolation + split + 2-face keys (steps 4-5), radix sort of the keys and
-// pairing into intersecting edges (step 5). Each layer starts with the
-// pre-activation evaluation (step 1) and a scan that records, per edge, the
-// first neuron of the layer whose sign differs at its endpoints (steps 2-3).
+// gfx950. One neuron step is: the split of its list of splitting edges
+// (interpolation, new vertices, 2-face keys into the hash table; steps 4-5), then
+// the pairing into intersecting edges (step 5), which also lists the next neuron's
+// splitting edges (step 3): two launches, three in large steps. With sort pairing
+// the list is compacted, the keys sorted and the pairs grouped in launches of their
+// own. Each layer starts with the pre-activation evaluation (step 1) and a scan that
+// records, per edge, the first neuron of the layer whose sign differs at its
+// endpoints (steps 2-3), and compacts the first neuron's list.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 #include <stdint.h>
@@ -207,8 +210,6 @@ __global__ __launch_bounds__(kBinThreads) void k_bin_scatter(const double *__res
 // two layers: 23.5 ms, 38.1 with every column in barrier-separated chunks of 8
 // whose ReLU waited for each load.
 constexpr int kEvalThreads = 256, kEvalRows = 32;
-typedef double dbl4 __attribute__((ext_vector_type(4)));
-
 template <int CW, int CT, int RT>
 __global__ __launch_bounds__(kEvalThreads, 4) void k_gemm_mfma(Bufs b, int ZS, const double *in, int in_stride,
                                                                int relu, int V, int K, int N,

@@ -9,7 +9,8 @@
 // the per-step path in worker threads, each on its own stream, so their kernels
 // overlap with the ticks and with each other; so does a small network that
 // would be alone in its tick while a worker is free (at low load the per-step
-// path answers it sooner). Every result is the complex pcx_extract returns for
+// path answers it sooner), and one that would hold its tick up while the workers'
+// queue is short. Every result is the complex pcx_extract returns for
 // the same request.
 #include <hip/hip_runtime.h>
 
@@ -37,9 +38,17 @@ struct BatchHolder {
 
 // Networks of up to this predicted size, with layers of at most kSmallWidth
 // neurons, always run in ticks; the other small ones on the workers while those
-// have at most kQueuePerWorker requests each before them. A burst of 16 requests
-// (D = 2 and 3, widths 16 to 32) takes 4.3 ms with 10,000, 4.4 with 16,000, 4.8
-// with 32,000 and 8.1 with every small request in the ticks.
+// have at most kQueuePerWorker requests each before them. Bursts of n requests,
+// from the first submission to the last completion (their results not copied out),
+// ms with this rule / every small request in the ticks / both before the
+// small-network kernel (medians; runs differ by 10%, D = 2 by more):
+//   D = 2 and 3, widths 16 to 32:   n = 16: 5.1 / 8.8 / 15;    48: 9.4 / 10.3 / 17
+//   D = 2 and 3, widths 8 to 40:    n = 16: 5.7 / 8.1 / 12;    96: 15.4 / 14.3 / 19
+//   D = 2, widths 16 to 64:         n = 16: 9.3 / 6 to 11 / 15 to 21;  96: 14 to 21 / 12 / 20 to 24
+//   D = 2, widths 65 to 100:        n = 24: 20 / 53 / 57 to 70;  96: 66 / 54 / 58 to 72
+//   D = 2 and 3, widths 16 to 128:  n = 48: 127 / - / 190
+// Four requests a worker instead of six: 46 ms for the 96 wide ones, but 139 for the
+// last row; 10,000 to 24,000 vertices within the runs' difference on the first two.
 constexpr double kTickVertices = 12000.0;
 constexpr int kQueuePerWorker = 6;
 
