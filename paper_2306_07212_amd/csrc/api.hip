@@ -1294,8 +1294,8 @@ int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad,
     // Everything the pass needs, before its first launch. Two arrays of gradient
     // rows take turns: a layer's start has fewer vertices than its end. The sort's
     // storage serves again after it (the records' values are not needed, and one of
-    // the two key arrays is free), so besides the rows a pass holds 56 bytes per new
-    // vertex and 8 per vertex.
+    // the two key arrays is free), so besides the rows a pass holds 64 bytes per new
+    // vertex (56 in FP32) and 8 per vertex.
     Arena ar;
     int rc;
     void *p;
@@ -1309,7 +1309,7 @@ int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad,
     double *part = nullptr;
     Bufs sb{};
     BwdChild<T> *child = nullptr;
-    static_assert(sizeof(BwdChild<T>) % sizeof(uint64_t) == 0, "whole words of the key array");
+    static_assert(alignof(BwdChild<T>) <= sizeof(uint64_t), "in the place of the keys");
     // (the records come in child order and the sort is stable: only the parents' bits are sorted)
     int key_bytes = 1;
     while (key_bytes < 4 && (cx->V >> (8 * key_bytes)) != 0) ++key_bytes;
@@ -1320,7 +1320,7 @@ int backward_impl(const pcx_mlp *mlp, const pcx_complex *cx, const double *grad,
         // (after the sort VALa holds the order by depth, VALb each parent's range of records)
         uint64_t *&sorted = key_bytes % 2 == 0 ? sb.K64a : sb.K64b, *&spare = key_bytes % 2 == 0 ? sb.K64b : sb.K64a;
         if (take(sorted, nrec) ||
-            take(spare, std::max((size_t)nrec, (size_t)(cx->V - Vb) * sizeof(BwdChild<T>) / sizeof(uint64_t))) ||
+            take(spare, std::max((size_t)nrec, ((size_t)(cx->V - Vb) * sizeof(BwdChild<T>) + 7) / 8)) ||
             take(sb.VALa, nrec) || take(sb.VALb, 2 * (size_t)cx->V) ||
             take(sb.HIST, (size_t)kSortBins * ((nrec + kSortTile - 1) / kSortTile + 1)) ||
             take(depths, (size_t)nsub * kDepths))

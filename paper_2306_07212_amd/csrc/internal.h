@@ -236,11 +236,12 @@ void bwd_ranges(const uint64_t *skey, int nrec, int V, int2 *range, hipStream_t 
 // from the depths' first places next[d] (overwritten), the vertices in order[]
 void bwd_depth_count(const uint32_t *DEP, int lw0, int Vs, int Ve, int *count, int *flag, hipStream_t st);
 void bwd_depth_order(const uint32_t *DEP, int lw0, int Vs, int Ve, int *next, int *order, hipStream_t st);
-// of a finished new vertex: t of its splitting edge, dL/dt, and dt/dz of its V+ and V- parent
+// of a finished new vertex: what its V+ and its V- parent multiply, its gradients by
+// s = 1 - t or t and dL/dt by f = dt/dz, and dL/dt
 template <typename T>
 struct BwdChild {
-    double t;
-    T gt, fp, fq;
+    T sf[2][2];  // [side] (s, f)
+    T gt;
 };
 // the arrays of a layer's reverse pass
 template <typename T>
