@@ -104,8 +104,8 @@ struct BatchRoom {
 // time, so with `spare` both are sized by D. Largest over 2,554 He networks of 1 to
 // 4 layers (V above 512 over the prediction; S, the largest step, over V):
 //   D = 3: 0.9, 0.17;  4: 1.6, 0.26;  5: 4.4, 0.32;  6: 14, 0.35;  8: 76, 0.44.
-// (Every workgroup clears its key slots for every network: no more spare of them
-// than 24K or twice the least.)
+// (The 256-thread kernel clears its key slots for every network: no more spare of
+// them than 24K or twice the least.)
 size_t least_vertices(double pred) { return (size_t)(pred * 1.25) + 64; }
 size_t vertex_room(int D, double pred, bool spare) {
     const size_t least = least_vertices(pred);

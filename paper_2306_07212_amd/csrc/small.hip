@@ -229,8 +229,6 @@ __device__ void run_small(const BatchArgs &A, const BatchNet &net, int ni, Small
         if (t < CTR_COUNT) s.ctr[t] = t == CTR_PFAIL ? 0x7fffffff : 0;
         for (int i = t; i < SmallLds<T>::TABLE; i += T) s.table[i] = 0ull;
         for (int i = t; i < SmallLds<T>::KEYS; i += T) s.part[i] = 0;
-        // partner records of an earlier network in this arena: untagged again
-        for (int i = t; i < Kcap; i += T) b.PART[i] = 0ull;
         // step 0: the box
         for (int i = t; i < V0 + E0; i += T) {
             if (i < V0) {
@@ -256,6 +254,7 @@ __device__ void run_small(const BatchArgs &A, const BatchNet &net, int ni, Small
     int V = V0, E = E0;
     long long splits = 0, pairs = 0;
     int step = 0;
+    bool untagged = false;  // the arena's partner records
     for (int l = 0; l < nsub && status == BATCH_OK; ++l) {
         const int N = net.widths[l + 1], K = net.widths[l];
         eval_strips<T>(b, ZS, l == 0 ? b.X : b.Z, l == 0 ? D : ZS, l > 0, V, K, N, net.Wt[l], net.b[l], Wd, lw[l]);
@@ -326,6 +325,10 @@ __device__ void run_small(const BatchArgs &A, const BatchNet &net, int ni, Small
                 for (int i = t; i < nslots; i += T) s.part[i] = 0;
             } else {
                 const LdsMem<T, false> m{&s, 0u, rest};
+                // (before the network's first such step: partner records of an earlier
+                // network in this arena untagged again)
+                for (int i = t; i < Kcap && !untagged; i += T) b.PART[i] = 0ull;
+                untagged = true;
                 for (uint32_t i = t; i < tsz; i += T) table[i] = 0ull;
                 __syncthreads();
                 if (N <= 32) small_split<T, 2>(b, g, s, m, V, E, S);
